@@ -263,9 +263,18 @@ int bfp_repack(const uint8_t* mant, const uint8_t* exp, int64_t rows, int64_t le
  *                 a workspace must not overlap.
  *   Size limits : as bfp_gemm, with K_out in place of K (BFP_E_UNSUPPORTED).
  *   BFP_E_ARG   : also for a workspace below the required size.
+ * With a workspace of at least bfp_gemm_ws_full_size bytes (>= bfp_gemm_ws_size)
+ * a product with few output tiles and a long K (a weight gradient, a few
+ * tokens) takes K in parts: the parts' FP32 sums go to the workspace and are
+ * added up in a fixed order by a second kernel.  A smaller workspace gives the
+ * same product with K summed in one run.  Products with few outputs run on a
+ * kernel of their own with either workspace (gemm_direct.h).  The order of the
+ * cross-group sum depends on the shape and the workspace only, never on the run.
  */
 int bfp_gemm_ws_size(int a_m_bits, int b_m_bits, int64_t M, int64_t N, int64_t K, int g, int m_a, int m_b, int packed,
                      size_t* bytes);
+int bfp_gemm_ws_full_size(int a_m_bits, int b_m_bits, int64_t M, int64_t N, int64_t K, int g, int m_a, int m_b,
+                          int packed, size_t* bytes);
 int bfp_gemm_ws(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, const uint8_t* b_mant, const uint8_t* b_exp,
                 int b_m_bits, int64_t M, int64_t N, int64_t K, int g, int m_a, int m_b, int packed, float* C,
                 int64_t ldc, void* workspace, size_t workspace_bytes, void* stream);
@@ -316,6 +325,22 @@ int bfp_gemm_tiled(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, co
 int bfp_gemm_bfp(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, const uint8_t* b_mant, const uint8_t* b_exp,
                  int b_m_bits, int64_t M, int64_t N, int64_t K, int g, int m_a, int m_b, int c_m_bits, int round_mode,
                  uint64_t seed, uint8_t* c_mant, uint8_t* c_exp, uint32_t* status_word, void* stream);
+
+/*
+ * bfp_gemm_bfp_ws -- bfp_gemm_bfp with a caller workspace (section V-A): exactly
+ * bfp_quantize(C, group axis 1, g = 16, ...) of the FP32 C that bfp_gemm_ws
+ * computes with a workspace of bfp_gemm_ws_full_size bytes.  Products that
+ * bfp_gemm_ws takes in parts or on the few-output kernel leave their FP32 sums
+ * in the workspace (bfp_gemm_bfp_ws_size bytes, 256-byte aligned), from which a
+ * second kernel converts them; the others need none (size 0, NULL).  With a
+ * smaller workspace it is bfp_gemm_bfp.
+ */
+int bfp_gemm_bfp_ws_size(int a_m_bits, int b_m_bits, int64_t M, int64_t N, int64_t K, int g, int m_a, int m_b,
+                         size_t* bytes);
+int bfp_gemm_bfp_ws(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, const uint8_t* b_mant,
+                    const uint8_t* b_exp, int b_m_bits, int64_t M, int64_t N, int64_t K, int g, int m_a, int m_b,
+                    int c_m_bits, int round_mode, uint64_t seed, uint8_t* c_mant, uint8_t* c_exp,
+                    uint32_t* status_word, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
  * bfp_gemm_group_partials -- the exact integer group dot products

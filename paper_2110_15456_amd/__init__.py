@@ -320,16 +320,20 @@ def _gemm_with_workspace(A, B, m_a, m_b, C, workspace):
     """bfp_gemm_ws: operands the block-scaled kernel cannot read as stored are
     repacked into a workspace (torch-allocated unless one is given)."""
     packed = 1 if isinstance(A, PackedBFPTensor) else 0
-    need = gemm_ws_size(A, B, m_a, m_b)
-    if need == 0:
-        ws = None
-    elif isinstance(workspace, torch.Tensor):
-        _need_cuda(workspace, "workspace", torch.uint8)
+    if isinstance(workspace, torch.Tensor):
+        need = gemm_ws_size(A, B, m_a, m_b)
         ws = workspace
-        if ws.numel() < need:
-            raise ValueError("workspace needs %d bytes" % need)
+        if need > 0:
+            _need_cuda(workspace, "workspace", torch.uint8)
+            if workspace.numel() < need:
+                raise ValueError("workspace needs %d bytes" % need)
+        elif not workspace.is_cuda or workspace.dtype != torch.uint8 or not workspace.is_contiguous():
+            ws = None  # none is needed
     else:
-        ws = torch.empty(need, dtype=torch.uint8, device=A.device)
+        nb = ctypes.c_size_t(0)
+        check(load().bfp_gemm_ws_full_size(A.m, B.m, A.rows, B.rows, A.len, A.g, m_a, m_b, packed, ctypes.byref(nb)),
+              "bfp_gemm_ws_full_size")
+        ws = torch.empty(nb.value, dtype=torch.uint8, device=A.device) if nb.value else None
     check(load().bfp_gemm_ws(ctypes.c_void_p(A.mant.data_ptr()), ctypes.c_void_p(A.exp.data_ptr()), A.m,
                              ctypes.c_void_p(B.mant.data_ptr()), ctypes.c_void_p(B.exp.data_ptr()), B.m, A.rows,
                              B.rows, A.len, A.g, m_a, m_b, packed, ctypes.c_void_p(C.data_ptr()), C.stride(0),
@@ -400,11 +404,16 @@ def gemm_bfp(A: BFPTensor, B: BFPTensor, c_m: int, m_a: int | None = None, m_b: 
     if status is not None:
         _need_cuda(status, "status")
         st_ptr = ctypes.c_void_p(status.data_ptr())
-    check(load().bfp_gemm_bfp(ctypes.c_void_p(A.mant.data_ptr()), ctypes.c_void_p(A.exp.data_ptr()), A.m,
-                              ctypes.c_void_p(B.mant.data_ptr()), ctypes.c_void_p(B.exp.data_ptr()), B.m, A.rows,
-                              B.rows, A.len, A.g, m_a, m_b, c_m, ROUNDING[rounding],
-                              ctypes.c_uint64(seed & 0xFFFFFFFFFFFFFFFF), ctypes.c_void_p(t.mant.data_ptr()),
-                              ctypes.c_void_p(t.exp.data_ptr()), st_ptr, _stream(A.device)), "bfp_gemm_bfp")
+    nb = ctypes.c_size_t(0)
+    check(load().bfp_gemm_bfp_ws_size(A.m, B.m, A.rows, B.rows, A.len, A.g, m_a, m_b, ctypes.byref(nb)), "bfp_gemm_bfp")
+    ws = torch.empty(nb.value, dtype=torch.uint8, device=A.device) if nb.value else None
+    check(load().bfp_gemm_bfp_ws(ctypes.c_void_p(A.mant.data_ptr()), ctypes.c_void_p(A.exp.data_ptr()), A.m,
+                                 ctypes.c_void_p(B.mant.data_ptr()), ctypes.c_void_p(B.exp.data_ptr()), B.m, A.rows,
+                                 B.rows, A.len, A.g, m_a, m_b, c_m, ROUNDING[rounding],
+                                 ctypes.c_uint64(seed & 0xFFFFFFFFFFFFFFFF), ctypes.c_void_p(t.mant.data_ptr()),
+                                 ctypes.c_void_p(t.exp.data_ptr()), st_ptr,
+                                 ctypes.c_void_p(ws.data_ptr()) if ws is not None else None, nb.value,
+                                 _stream(A.device)), "bfp_gemm_bfp")
     return t
 
 

@@ -122,6 +122,11 @@ int ws_plan(int a_m, int b_m, int64_t M, int64_t N, int64_t K, int g, int m_a, i
   return BFP_OK;
 }
 
+// Bytes of the partial-sum matrices of a product taken in parts.
+size_t parts_bytes(int parts, int64_t M, int64_t N) {
+  return align256((size_t)parts * (size_t)M * (size_t)fastbfp::gemm_plan_ld(N) * sizeof(float));
+}
+
 int check_dual(const float* x, int64_t R, int64_t C, int g, int m_bits, int round_mode, const uint8_t* mr,
                const uint8_t* er, const uint8_t* mc, const uint8_t* ec, const uint32_t* status_word) {
   if (round_mode < BFP_ROUND_NEAREST || round_mode > BFP_ROUND_TRUNCATE) return BFP_E_ARG;
@@ -258,9 +263,10 @@ int bfp_gemm(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, const ui
   return bfp_gemm_tiled(a_mant, a_exp, a_m_bits, b_mant, b_exp, b_m_bits, M, N, K, g, m_a, m_b, C, ldc, -1, stream);
 }
 
-int bfp_gemm_bfp(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, const uint8_t* b_mant, const uint8_t* b_exp,
-                 int b_m_bits, int64_t M, int64_t N, int64_t K, int g, int m_a, int m_b, int c_m_bits, int round_mode,
-                 uint64_t seed, uint8_t* c_mant, uint8_t* c_exp, uint32_t* status_word, void* stream) {
+static int check_gemm_bfp(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, const uint8_t* b_mant,
+                          const uint8_t* b_exp, int b_m_bits, int64_t M, int64_t N, int64_t K, int g, int m_a, int m_b,
+                          int c_m_bits, int round_mode, const uint8_t* c_mant, const uint8_t* c_exp,
+                          const uint32_t* status_word) {
   int st = check_gemm(a_mant, a_m_bits, b_mant, b_m_bits, M, N, K, g, m_a, m_b);
   if (st != BFP_OK) return st;
   if (!fast_path(a_m_bits, b_m_bits, g, m_a, m_b)) return BFP_E_UNSUPPORTED;
@@ -270,10 +276,57 @@ int bfp_gemm_bfp(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, cons
   if (M == 0 || N == 0) return BFP_OK;
   if (!c_mant || !c_exp || (K > 0 && (!a_exp || !b_exp))) return BFP_E_ARG;
   if (!aligned(c_mant, 4) || !aligned(status_word, 4)) return BFP_E_ARG;
+  return BFP_OK;
+}
+
+int bfp_gemm_bfp(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, const uint8_t* b_mant, const uint8_t* b_exp,
+                 int b_m_bits, int64_t M, int64_t N, int64_t K, int g, int m_a, int m_b, int c_m_bits, int round_mode,
+                 uint64_t seed, uint8_t* c_mant, uint8_t* c_exp, uint32_t* status_word, void* stream) {
+  const int st = check_gemm_bfp(a_mant, a_exp, a_m_bits, b_mant, b_exp, b_m_bits, M, N, K, g, m_a, m_b, c_m_bits,
+                                round_mode, c_mant, c_exp, status_word);
+  if (st != BFP_OK || M == 0 || N == 0) return st;
   const int na = planes_used(a_m_bits, m_a), nb = planes_used(b_m_bits, m_b);
   return status_of(fastbfp::launch_gemm_mx_bfp(a_mant, a_exp, a_m_bits, na, b_mant, b_exp, b_m_bits, nb, M, N, K, g,
                                                4 - m_a - m_b, c_m_bits, round_mode, seed, c_mant, c_exp, status_word,
                                                static_cast<hipStream_t>(stream)));
+}
+
+int bfp_gemm_bfp_ws_size(int a_m_bits, int b_m_bits, int64_t M, int64_t N, int64_t K, int g, int m_a, int m_b,
+                         size_t* bytes) {
+  if (!bytes) return BFP_E_ARG;
+  const int st = check_gemm_shape(a_m_bits, b_m_bits, M, N, K, g, m_a, m_b);
+  if (st != BFP_OK) return st;
+  if (!fast_path(a_m_bits, b_m_bits, g, m_a, m_b)) return BFP_E_UNSUPPORTED;
+  if (N % 16 != 0) return BFP_E_SHAPE;
+  *bytes = 0;
+  if (M == 0 || N == 0) return BFP_OK;
+  const fastbfp::GemmPlan plan =
+      fastbfp::gemm_plan(a_m_bits, planes_used(a_m_bits, m_a), b_m_bits, planes_used(b_m_bits, m_b), M, N, K, g);
+  if (plan.parts > 1 || plan.rm > 0) *bytes = parts_bytes(plan.parts, M, N);
+  return BFP_OK;
+}
+
+int bfp_gemm_bfp_ws(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, const uint8_t* b_mant,
+                    const uint8_t* b_exp, int b_m_bits, int64_t M, int64_t N, int64_t K, int g, int m_a, int m_b,
+                    int c_m_bits, int round_mode, uint64_t seed, uint8_t* c_mant, uint8_t* c_exp,
+                    uint32_t* status_word, void* workspace, size_t workspace_bytes, void* stream) {
+  int st = check_gemm_bfp(a_mant, a_exp, a_m_bits, b_mant, b_exp, b_m_bits, M, N, K, g, m_a, m_b, c_m_bits, round_mode,
+                          c_mant, c_exp, status_word);
+  if (st != BFP_OK || M == 0 || N == 0) return st;
+  const int na = planes_used(a_m_bits, m_a), nb = planes_used(b_m_bits, m_b);
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  const fastbfp::GemmPlan plan = fastbfp::gemm_plan(a_m_bits, na, b_m_bits, nb, M, N, K, g);
+  if ((plan.parts == 1 && plan.rm == 0) || !workspace || !aligned(workspace, 256) ||
+      workspace_bytes < parts_bytes(plan.parts, M, N))
+    return status_of(fastbfp::launch_gemm_mx_bfp(a_mant, a_exp, a_m_bits, na, b_mant, b_exp, b_m_bits, nb, M, N, K, g,
+                                                 4 - m_a - m_b, c_m_bits, round_mode, seed, c_mant, c_exp, status_word,
+                                                 s));
+  float* parts = static_cast<float*>(workspace);
+  st = status_of(fastbfp::launch_gemm_plan(plan, a_mant, a_exp, a_m_bits, na, b_mant, b_exp, b_m_bits, nb, M, N, K, g,
+                                           4 - m_a - m_b, parts, N, s));
+  if (st != BFP_OK) return st;
+  return status_of(fastbfp::launch_parts_convert(parts, plan.parts, M, N, c_m_bits, round_mode, seed, c_mant, c_exp,
+                                                 status_word, s));
 }
 
 int bfp_gemm_group_partials(const uint8_t* a_mant, int a_m_bits, const uint8_t* b_mant, int b_m_bits, int64_t M,
@@ -384,6 +437,28 @@ int bfp_gemm_ws_size(int a_m_bits, int b_m_bits, int64_t M, int64_t N, int64_t K
   return BFP_OK;
 }
 
+// The plan of a product through bfp_gemm_ws: on the operands as the kernel will
+// read them.
+static fastbfp::GemmPlan plan_of(const WsPlan& p, int a_m, int b_m, int64_t M, int64_t N, int m_a, int m_b) {
+  const int sa = p.rep_a ? m_a : a_m, sb = p.rep_b ? m_b : b_m;  // stored widths the kernel sees
+  return fastbfp::gemm_plan(sa, planes_used(sa, m_a), sb, planes_used(sb, m_b), M, N, p.k_out, p.g_out);
+}
+
+int bfp_gemm_ws_full_size(int a_m_bits, int b_m_bits, int64_t M, int64_t N, int64_t K, int g, int m_a, int m_b,
+                          int packed, size_t* bytes) {
+  if (!bytes) return BFP_E_ARG;
+  int st = check_gemm_shape(a_m_bits, b_m_bits, M, N, K, g, m_a, m_b);
+  if (st != BFP_OK) return st;
+  WsPlan p;
+  st = ws_plan(a_m_bits, b_m_bits, M, N, K, g, m_a, m_b, packed, &p);
+  if (st != BFP_OK) return st;
+  *bytes = p.bytes;
+  if (M == 0 || N == 0) return BFP_OK;
+  const fastbfp::GemmPlan plan = plan_of(p, a_m_bits, b_m_bits, M, N, m_a, m_b);
+  if (plan.parts > 1) *bytes += parts_bytes(plan.parts, M, N);
+  return BFP_OK;
+}
+
 int bfp_gemm_ws(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, const uint8_t* b_mant, const uint8_t* b_exp,
                 int b_m_bits, int64_t M, int64_t N, int64_t K, int g, int m_a, int m_b, int packed, float* C,
                 int64_t ldc, void* workspace, size_t workspace_bytes, void* stream) {
@@ -420,8 +495,22 @@ int bfp_gemm_ws(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, const
       bm = om, be = oe;
     }
   }
-  return status_of(fastbfp::launch_gemm_mx(am, ae, a_m, planes_used(a_m, m_a), bm, be, b_m, planes_used(b_m, m_b), M,
-                                           N, p.k_out, p.g_out, 4 - m_a - m_b, C, ldc, -1, s));
+  const int na = planes_used(a_m, m_a), nb = planes_used(b_m, m_b);
+  fastbfp::GemmPlan plan = fastbfp::gemm_plan(a_m, na, b_m, nb, M, N, p.k_out, p.g_out);
+  const int exp2 = 4 - m_a - m_b;
+  // in parts only where the workspace holds their sums
+  const bool split = plan.parts > 1 && workspace && aligned(workspace, 256) &&
+                     workspace_bytes >= p.bytes + parts_bytes(plan.parts, M, N);
+  if (!split) {
+    plan.parts = 1;
+    return status_of(fastbfp::launch_gemm_plan(plan, am, ae, a_m, na, bm, be, b_m, nb, M, N, p.k_out, p.g_out, exp2, C,
+                                               ldc, s));
+  }
+  float* parts = reinterpret_cast<float*>(ws + p.bytes);
+  st = status_of(fastbfp::launch_gemm_plan(plan, am, ae, a_m, na, bm, be, b_m, nb, M, N, p.k_out, p.g_out, exp2, parts,
+                                           fastbfp::gemm_plan_ld(N), s));
+  if (st != BFP_OK) return st;
+  return status_of(fastbfp::launch_parts_sum(parts, plan.parts, M, N, C, ldc, s));
 }
 
 int bfp_quantize_dual(const float* x, int64_t R, int64_t C, int g, int m_bits, int round_mode, uint64_t seed_r,

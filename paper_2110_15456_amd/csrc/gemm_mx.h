@@ -182,16 +182,28 @@ __device__ __forceinline__ void tile_of(int bid, int nblocks, int tiles_m, int t
   tn = in / rows_in_group;
 }
 
-// Exponents of one slab for one row (EK bytes of ng_e per row), zero past
-// the last group and for rows past the end.  dw: every row starts 4-byte
+// The same with the K slabs split into parts (workgroup id -> tile and part):
+// the tiles of one part, which share its operand panels, follow one another on
+// one XCD.  (Any workgroup count: the first nblocks % 8 XCDs take one more.)
+template <int GROUP_M>
+__device__ __forceinline__ int split_tile_of(int bid, int nblocks, int tiles_m, int tiles_n, int& tm, int& tn) {
+  constexpr int NXCD = 8;
+  const int xcd = bid % NXCD, lid = xcd * (nblocks / NXCD) + min(xcd, nblocks % NXCD) + bid / NXCD;
+  const int tiles = tiles_m * tiles_n, part = lid / tiles;
+  tile_of<GROUP_M>(lid - part * tiles, 1, tiles_m, tiles_n, tm, tn);
+  return part;
+}
+
+// Exponents of one slab for one row (EK bytes, rows `stride` bytes apart, ng
+// of them left in each), zero past the last group and for rows past the end.  dw: every row starts 4-byte
 // aligned and holds a multiple of 4 exponents (K a multiple of 4 groups), so
 // a slab's valid bytes are whole dwords: one dword load per 4 exponents
 // instead of one byte load each (the ragged-K ResNet shape, K = 576).
 template <int EK>
-__device__ __forceinline__ uint2 load_exps(const uint8_t* __restrict__ exps, int row, int row_end, int ng, int slab,
-                                           bool dw) {
+__device__ __forceinline__ uint2 load_exps(const uint8_t* __restrict__ exps, int row, int row_end, int stride, int ng,
+                                           int slab, bool dw) {
   const bool rok = row < row_end;
-  const int64_t base = (int64_t)(rok ? row : 0) * ng + slab * EK;
+  const int64_t base = (int64_t)(rok ? row : 0) * stride + slab * EK;
   const int gvalid = min(EK, ng - slab * EK);
   uint32_t w[2] = {0u, 0u};
   if (dw) {
@@ -436,7 +448,8 @@ __global__ __launch_bounds__(CF::NT) void k_gemm_mx(const uint8_t* __restrict__ 
                                                  int64_t a_plane_stride, const uint8_t* __restrict__ b_mant,
                                                  const uint8_t* __restrict__ b_exp, int64_t b_plane_stride, int M,
                                                  int N, int ng, float scale, float* __restrict__ C, int64_t ldc,
-                                                 int tiles_m, int tiles_n, OutBFP qo) {
+                                                 int tiles_m, int tiles_n, int part_slabs, int64_t part_stride,
+                                                 OutBFP qo) {
   constexpr int TM = CF::TM, TN = CF::TN, NA = CF::NA, NB = CF::NB, FA = CF::FA, FB = CF::FB;
   // Groups of 16 with full slabs (XP): the exponents of slab pair p (slabs 2p
   // and 2p + 1: 16 contiguous bytes per row) come in one 16-byte load per row,
@@ -464,7 +477,17 @@ __global__ __launch_bounds__(CF::NT) void k_gemm_mx(const uint8_t* __restrict__ 
   __shared__ __attribute__((aligned(16))) uint8_t sink[CF::NW * 256];  // destination of padding loads, never read
   const int tid = threadIdx.x;
   int tm, tn;
-  tile_of<FASTBFP_MX_GM>(blockIdx.x, gridDim.x, tiles_m, tiles_n, tm, tn);
+  // K in parts (part_slabs > 0): this workgroup sums slabs [slab0, slab0 +
+  // part_slabs) into its part's own FP32 matrix, part_stride values after the
+  // previous one (launch_split_sum adds them up).
+  int slab0 = 0;
+  if (QNCH == 0 && part_slabs > 0) {
+    const int part = split_tile_of<FASTBFP_MX_GM>(blockIdx.x, gridDim.x, tiles_m, tiles_n, tm, tn);
+    slab0 = part * part_slabs;
+    C += part * part_stride;
+  } else {
+    tile_of<FASTBFP_MX_GM>(blockIdx.x, gridDim.x, tiles_m, tiles_n, tm, tn);
+  }
   const int row0 = tm * CF::BM, col0 = tn * CF::BN;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;  // wave index in an SGPR
   const int wr = wave / CF::WGN, wc = wave % CF::WGN;
@@ -484,12 +507,14 @@ __global__ __launch_bounds__(CF::NT) void k_gemm_mx(const uint8_t* __restrict__ 
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
 
-  const int nslabs = (ng + mx::KG - 1) / mx::KG;
+  const int ngl = ng - slab0 * mx::KG;  // 16-value halves from this part's first slab to the rows' end
+  const int all_slabs = (ngl + mx::KG - 1) / mx::KG;
+  const int nslabs = (QNCH == 0 && part_slabs > 0) ? min(part_slabs, all_slabs) : all_slabs;
   auto exp_row = [&](int k, const uint8_t*& src, int& grow, int& gend, int& lds) {
     const int r = tid + k * CF::NT;
     const bool is_a = r < CF::BM;
     const int rr = is_a ? r : r - CF::BM;
-    src = is_a ? a_exp : b_exp;
+    src = (is_a ? a_exp : b_exp) + slab0 * CF::EK;
     grow = (is_a ? row0 : col0) + rr;
     gend = is_a ? M : N;
     lds = (is_a ? CF::OFF_EA : CF::OFF_EB) + rr * CF::EK;
@@ -503,12 +528,14 @@ __global__ __launch_bounds__(CF::NT) void k_gemm_mx(const uint8_t* __restrict__ 
 #pragma unroll
   for (int p = 0; p < NA; ++p) {
     const uint32_t r = rbytes(mx::a_four<CF>(p));
-    ra[p] = make_rsrc(a_mant + p * a_plane_stride + (int64_t)row0 * r, (uint32_t)a_rows * r);
+    const uint32_t o = (uint32_t)slab0 * (mx::a_four<CF>(p) ? mx::KG * 8u : mx::KG * 12u);  // the part's first slab
+    ra[p] = make_rsrc(a_mant + p * a_plane_stride + (int64_t)row0 * r + o, (uint32_t)a_rows * r - o);
   }
 #pragma unroll
   for (int p = 0; p < NB; ++p) {
     const uint32_t r = rbytes(mx::b_four<CF>(p));
-    rb[p] = make_rsrc(b_mant + p * b_plane_stride + (int64_t)col0 * r, (uint32_t)b_rows * r);
+    const uint32_t o = (uint32_t)slab0 * (mx::b_four<CF>(p) ? mx::KG * 8u : mx::KG * 12u);
+    rb[p] = make_rsrc(b_mant + p * b_plane_stride + (int64_t)col0 * r + o, (uint32_t)b_rows * r - o);
   }
   // FP6: lane -> (row lane / 8 of the instruction's 8, slot lane % 8), loading
   // the group that the row's swizzle puts in that slot.
@@ -520,8 +547,9 @@ __global__ __launch_bounds__(CF::NT) void k_gemm_mx(const uint8_t* __restrict__ 
   const int ng_e = ng * 16 / CF::G;
   const bool exp_dw = (ng_e & 3) == 0 && (reinterpret_cast<uintptr_t>(a_exp) & 3) == 0 &&
                       (reinterpret_cast<uintptr_t>(b_exp) & 3) == 0;
-  const rsrc_t rea = make_rsrc(a_exp + (int64_t)row0 * ng_e, (uint32_t)(a_rows * ng_e));
-  const rsrc_t reb = make_rsrc(b_exp + (int64_t)col0 * ng_e, (uint32_t)(b_rows * ng_e));
+  const int eo = slab0 * CF::EK;
+  const rsrc_t rea = make_rsrc(a_exp + (int64_t)row0 * ng_e + eo, (uint32_t)(a_rows * ng_e - eo));
+  const rsrc_t reb = make_rsrc(b_exp + (int64_t)col0 * ng_e + eo, (uint32_t)(b_rows * ng_e - eo));
   constexpr int DPR = CF::EK / 4;
   const uint32_t e_lane_off = (uint32_t)(lane / DPR) * (uint32_t)ng_e + (uint32_t)(lane % DPR) * 4u;
   const uint32_t x_lane_off = (uint32_t)lane * (uint32_t)ng_e;
@@ -567,11 +595,11 @@ __global__ __launch_bounds__(CF::NT) void k_gemm_mx(const uint8_t* __restrict__ 
         const uint8_t* src;
         int grow, gend, lds;
         exp_row(k, src, grow, gend, lds);
-        e[k] = load_exps<CF::EK>(src, grow, gend, ng_e, slab, exp_dw);
+        e[k] = load_exps<CF::EK>(src, grow, gend, ng_e, ng_e - eo, slab, exp_dw);
       }
     }
-    const bool g_ok = slab * mx::KG + g_lane < ng;
-    const bool p_ok = slab * mx::KG + 2 * p_lane < ng;
+    const bool g_ok = slab * mx::KG + g_lane < ngl;
+    const bool p_ok = slab * mx::KG + 2 * p_lane < ngl;
 #pragma unroll
     for (int p = 0; p < NA; ++p) {
       if (mx::a_four<CF>(p))
@@ -1132,21 +1160,26 @@ __global__ __launch_bounds__(CF::NT) void k_gemm_mx(const uint8_t* __restrict__ 
   }
 }
 
+// part_slabs > 0: K in parts of that many slabs (an even number: the exponents
+// of slabs come in pairs), part p's sums to the M x ldc matrix at C + p M ldc.
 template <class CF, bool EXP_FULL>
 static hipError_t launch_mx_v(const uint8_t* a_mant, const uint8_t* a_exp, int64_t a_ps, const uint8_t* b_mant,
                               const uint8_t* b_exp, int64_t b_ps, int M, int N, int ng, float scale, float* C,
-                              int64_t ldc, const OutBFP* qo, hipStream_t s) {
+                              int64_t ldc, const OutBFP* qo, int part_slabs, hipStream_t s) {
   const int tiles_m = (M + CF::BM - 1) / CF::BM, tiles_n = (N + CF::BN - 1) / CF::BN;
-  const dim3 grid((unsigned)(tiles_m * tiles_n)), block(CF::NT);
+  const int slabs = (ng + mx::KG - 1) / mx::KG;
+  const int parts = part_slabs > 0 ? (slabs + part_slabs - 1) / part_slabs : 1;
+  const dim3 grid((unsigned)(tiles_m * tiles_n * parts)), block(CF::NT);
+  const int64_t stride = (int64_t)M * ldc;
   if (!qo)
-    hipLaunchKernelGGL((k_gemm_mx<CF, EXP_FULL, 0>), grid, dim3(CF::NT), 0, s, a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, M, N,
-                       ng, scale, C, ldc, tiles_m, tiles_n, OutBFP{});
+    hipLaunchKernelGGL((k_gemm_mx<CF, EXP_FULL, 0>), grid, block, 0, s, a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, M, N,
+                       ng, scale, C, ldc, tiles_m, tiles_n, part_slabs, stride, OutBFP{});
   else if (qo->m > 4)
     hipLaunchKernelGGL((k_gemm_mx<CF, EXP_FULL, 2>), grid, block, 0, s, a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, M, N,
-                       ng, scale, C, ldc, tiles_m, tiles_n, *qo);
+                       ng, scale, C, ldc, tiles_m, tiles_n, 0, stride, *qo);
   else
     hipLaunchKernelGGL((k_gemm_mx<CF, EXP_FULL, 1>), grid, block, 0, s, a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, M, N,
-                       ng, scale, C, ldc, tiles_m, tiles_n, *qo);
+                       ng, scale, C, ldc, tiles_m, tiles_n, 0, stride, *qo);
   return hipGetLastError();
 }
 
@@ -1156,7 +1189,7 @@ static hipError_t launch_mx_v(const uint8_t* a_mant, const uint8_t* a_exp, int64
 template <int NA, int NB, int FA, int FB, int G>
 hipError_t launch_mx_t(const uint8_t* a_mant, const uint8_t* a_exp, int64_t a_ps, const uint8_t* b_mant,
                        const uint8_t* b_exp, int64_t b_ps, int M, int N, int ng, float scale, float* C, int64_t ldc,
-                       const OutBFP* qo, hipStream_t s) {
+                       const OutBFP* qo, int part_slabs, hipStream_t s) {
   // The tile shrinks along an operand with two chunk planes so that two LDS
   // stages fit in 160 KB; with FP4 upper planes on both sides (192 bytes per
   // slab row instead of 256) A keeps 256 rows.
@@ -1167,8 +1200,10 @@ hipError_t launch_mx_t(const uint8_t* a_mant, const uint8_t* a_exp, int64_t a_ps
   auto al = [](const void* p, uintptr_t a) { return reinterpret_cast<uintptr_t>(p) % a == 0; };
   // direct exponent loads need full slabs and 4-byte aligned exponent rows
   const bool ef = ng % mx::KG == 0 && al(a_exp, 4) && al(b_exp, 4);  // (K a multiple of 128 either way)
-  if (ef) return launch_mx_v<CF, true>(a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, M, N, ng, scale, C, ldc, qo, s);
-  return launch_mx_v<CF, false>(a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, M, N, ng, scale, C, ldc, qo, s);
+  if (ef) return launch_mx_v<CF, true>(a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, M, N, ng, scale, C, ldc, qo,
+                               part_slabs, s);
+  return launch_mx_v<CF, false>(a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, M, N, ng, scale, C, ldc, qo,
+                               part_slabs, s);
 }
 
 // One chunk plane per operand, groups of 16, on a BM x BN tile smaller than
@@ -1179,31 +1214,33 @@ hipError_t launch_mx_t(const uint8_t* a_mant, const uint8_t* a_exp, int64_t a_ps
 template <int BM, int BN, int FA, int FB>
 hipError_t launch_mx_11_tile(const uint8_t* a_mant, const uint8_t* a_exp, const uint8_t* b_mant,
                              const uint8_t* b_exp, int M, int N, int ng, float scale, float* C, int64_t ldc,
-                             const OutBFP* qo, hipStream_t s) {
+                             const OutBFP* qo, int part_slabs, hipStream_t s) {
   using CF = mx::Cfg<BM, BN, 1, 1, FA, FB, 16>;
   auto al = [](const void* p, uintptr_t a) { return reinterpret_cast<uintptr_t>(p) % a == 0; };
   const bool ef = ng % mx::KG == 0 && al(a_exp, 4) && al(b_exp, 4);
-  if (ef) return launch_mx_v<CF, true>(a_mant, a_exp, 0, b_mant, b_exp, 0, M, N, ng, scale, C, ldc, qo, s);
-  return launch_mx_v<CF, false>(a_mant, a_exp, 0, b_mant, b_exp, 0, M, N, ng, scale, C, ldc, qo, s);
+  if (ef) return launch_mx_v<CF, true>(a_mant, a_exp, 0, b_mant, b_exp, 0, M, N, ng, scale, C, ldc, qo,
+                               part_slabs, s);
+  return launch_mx_v<CF, false>(a_mant, a_exp, 0, b_mant, b_exp, 0, M, N, ng, scale, C, ldc, qo,
+                               part_slabs, s);
 }
 
 #define FASTBFP_MX11_TILE_DECLARE(BM, BN, FA, FB)                                                              \
   extern template hipError_t launch_mx_11_tile<BM, BN, FA, FB>(const uint8_t*, const uint8_t*, const uint8_t*, \
                                                                const uint8_t*, int, int, int, float, float*,   \
-                                                               int64_t, const OutBFP*, hipStream_t);
+                                                               int64_t, const OutBFP*, int, hipStream_t);
 #define FASTBFP_MX11_TILE_INSTANTIATE(BM, BN, FA, FB)                                                         \
   template hipError_t launch_mx_11_tile<BM, BN, FA, FB>(const uint8_t*, const uint8_t*, const uint8_t*,       \
                                                         const uint8_t*, int, int, int, float, float*, int64_t, \
-                                                        const OutBFP*, hipStream_t);
+                                                        const OutBFP*, int, hipStream_t);
 
 #define FASTBFP_MX_DECLARE(NA, NB, FA, FB, G)                                                          \
   extern template hipError_t launch_mx_t<NA, NB, FA, FB, G>(const uint8_t*, const uint8_t*, int64_t,       \
                                                             const uint8_t*, const uint8_t*, int64_t, int, int, \
-                                                            int, float, float*, int64_t, const OutBFP*,         \
+                                                            int, float, float*, int64_t, const OutBFP*, int,    \
                                                             hipStream_t);
 #define FASTBFP_MX_INSTANTIATE(NA, NB, FA, FB, G)                                                           \
   template hipError_t launch_mx_t<NA, NB, FA, FB, G>(const uint8_t*, const uint8_t*, int64_t, const uint8_t*, \
                                                      const uint8_t*, int64_t, int, int, int, float, float*,     \
-                                                     int64_t, const OutBFP*, hipStream_t);
+                                                     int64_t, const OutBFP*, int, hipStream_t);
 
 }  // namespace fastbfp

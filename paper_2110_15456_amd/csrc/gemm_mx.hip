@@ -3,6 +3,7 @@
 // and whether the first plane holds FP4 codes.  Each group size and
 // plane-count pair is instantiated in its own file
 // (gemm_mx_{11,12,21,22}[_g32].hip) so that they compile in parallel.
+#include "gemm_direct.h"
 #include "gemm_mx.h"
 
 namespace fastbfp {
@@ -49,6 +50,14 @@ FASTBFP_MX11_TILES_DECLARE(0, 0)
 FASTBFP_MX11_TILES_DECLARE(0, 1)
 FASTBFP_MX11_TILES_DECLARE(1, 0)
 FASTBFP_MX11_TILES_DECLARE(1, 1)
+FASTBFP_DIRECT_ALL(FASTBFP_DIRECT_DECLARE, 1, 1, 16)
+FASTBFP_DIRECT_ALL(FASTBFP_DIRECT_DECLARE, 1, 2, 16)
+FASTBFP_DIRECT_ALL(FASTBFP_DIRECT_DECLARE, 2, 1, 16)
+FASTBFP_DIRECT_ALL(FASTBFP_DIRECT_DECLARE, 2, 2, 16)
+FASTBFP_DIRECT_ALL(FASTBFP_DIRECT_DECLARE, 1, 1, 32)
+FASTBFP_DIRECT_ALL(FASTBFP_DIRECT_DECLARE, 1, 2, 32)
+FASTBFP_DIRECT_ALL(FASTBFP_DIRECT_DECLARE, 2, 1, 32)
+FASTBFP_DIRECT_ALL(FASTBFP_DIRECT_DECLARE, 2, 2, 32)
 
 // Tile of the one-chunk, groups-of-16, FP32-output GEMM (0..4: 256x256,
 // 256x128, 256x64, 128x64, 128x128), from measurements on MI355X over the
@@ -74,80 +83,235 @@ static int gemm_mx11_tile(int64_t M, int64_t N, int fa, bool converted) {
   return tiles(128, 128) >= MIN_TILES ? 4 : 3;
 }
 
-template <int FA, int FB>
-static hipError_t launch_11_tile(int t, const uint8_t* a_mant, const uint8_t* a_exp, const uint8_t* b_mant,
-                                 const uint8_t* b_exp, int M, int N, int ng, float scale, float* C, int64_t ldc,
-                                 const OutBFP* qo, hipStream_t s) {
-  if (t == 1) return launch_mx_11_tile<256, 128, FA, FB>(a_mant, a_exp, b_mant, b_exp, M, N, ng, scale, C, ldc, qo, s);
-  if (t == 2) return launch_mx_11_tile<256, 64, FA, FB>(a_mant, a_exp, b_mant, b_exp, M, N, ng, scale, C, ldc, qo, s);
-  if (t == 4) return launch_mx_11_tile<128, 128, FA, FB>(a_mant, a_exp, b_mant, b_exp, M, N, ng, scale, C, ldc, qo, s);
-  return launch_mx_11_tile<128, 64, FA, FB>(a_mant, a_exp, b_mant, b_exp, M, N, ng, scale, C, ldc, qo, s);
+namespace {
+
+// A product's operands as the kernels see them.
+struct Product {
+  const uint8_t *a_mant, *a_exp;
+  int64_t a_ps;  // byte offset of A's plane 1 (its stored plane 0's size)
+  const uint8_t *b_mant, *b_exp;
+  int64_t b_ps;
+  int M, N, ng;  // ng: 16-value halves per row (K / 16, the plane layout's unit)
+  int na, nb;    // planes read
+  int fa, fb;    // one plane read: it holds FP4 codes; two: split at 2 bits
+  float scale;
+};
+
+// Where C goes: FP32 rows, BFP in the epilogue (qo), or the partial sums of a
+// product whose K is taken in parts.
+struct Output {
+  float* C;
+  int64_t ldc;
+  const OutBFP* qo;
+  int part_slabs;  // 0: all of K
+  hipStream_t s;
+};
+
+template <int BM, int BN>
+hipError_t launch_tile(const Product& p, const Output& o) {
+#define FASTBFP_TILE(FA, FB)                                                                                         \
+  return launch_mx_11_tile<BM, BN, FA, FB>(p.a_mant, p.a_exp, p.b_mant, p.b_exp, p.M, p.N, p.ng, p.scale, o.C, o.ldc, \
+                                           o.qo, o.part_slabs, o.s)
+  if (!p.fa && !p.fb) FASTBFP_TILE(0, 0);
+  if (!p.fa) FASTBFP_TILE(0, 1);
+  if (!p.fb) FASTBFP_TILE(1, 0);
+  FASTBFP_TILE(1, 1);
+#undef FASTBFP_TILE
 }
 
 template <int NA, int NB, int G>
-static hipError_t launch_fmt(int fa, int fb, const uint8_t* a_mant, const uint8_t* a_exp, int64_t a_ps,
-                             const uint8_t* b_mant, const uint8_t* b_exp, int64_t b_ps, int M, int N, int ng,
-                             float scale, float* C, int64_t ldc, const OutBFP* qo, hipStream_t s) {
-  if (!fa && !fb) return launch_mx_t<NA, NB, 0, 0, G>(a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, M, N, ng, scale, C, ldc, qo, s);
-  if (!fa) return launch_mx_t<NA, NB, 0, 1, G>(a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, M, N, ng, scale, C, ldc, qo, s);
-  if (!fb) return launch_mx_t<NA, NB, 1, 0, G>(a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, M, N, ng, scale, C, ldc, qo, s);
-  return launch_mx_t<NA, NB, 1, 1, G>(a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, M, N, ng, scale, C, ldc, qo, s);
+hipError_t launch_fmt(const Product& p, const Output& o) {
+#define FASTBFP_FMT(FA, FB)                                                                                      \
+  return launch_mx_t<NA, NB, FA, FB, G>(p.a_mant, p.a_exp, p.a_ps, p.b_mant, p.b_exp, p.b_ps, p.M, p.N, p.ng,    \
+                                        p.scale, o.C, o.ldc, o.qo, o.part_slabs, o.s)
+  if (!p.fa && !p.fb) FASTBFP_FMT(0, 0);
+  if (!p.fa) FASTBFP_FMT(0, 1);
+  if (!p.fb) FASTBFP_FMT(1, 0);
+  FASTBFP_FMT(1, 1);
+#undef FASTBFP_FMT
 }
 
-// a_m / b_m: the stored operands' widths (they fix the plane formats and the
-// plane stride); na / nb: planes read; g: the group size.
+// tile: 0 the operand formats' default, 1..4 the smaller ones (one plane per
+// operand and groups of 16).
 template <int G>
-static hipError_t launch_gemm_g(const uint8_t* a_mant, const uint8_t* a_exp, int a_m, int na, const uint8_t* b_mant,
-                                const uint8_t* b_exp, int b_m, int nb, int64_t M, int64_t N, int64_t K, int scale_log2,
-                                float* C, int64_t ldc, const OutBFP* qo, int tile, hipStream_t s) {
-  if (M == 0 || N == 0) return hipSuccess;
-  const int ng = (int)(K / 16);  // 16-value halves per row (the plane layout's unit)
-  const int64_t a_ps = M * (K / G) * plane_group_bytes(G, a_m, 0), b_ps = N * (K / G) * plane_group_bytes(G, b_m, 0);
-  // the kernels' FA / FB: one plane read, FP4 codes; two, split at 2 bits
-  const int fa = na == 1 ? plane0_fp4(a_m) : a_m <= 6, fb = nb == 1 ? plane0_fp4(b_m) : b_m <= 6;
-  const float scale = ldexpf(1.0f, scale_log2);
-  const int m = (int)M, n = (int)N;
-  if (G == 16 && na == 1 && nb == 1) {
-    const int t = tile >= 0 ? tile : gemm_mx11_tile(M, N, fa, qo != nullptr);
-    if (t != 0) {
-      if (!fa && !fb) return launch_11_tile<0, 0>(t, a_mant, a_exp, b_mant, b_exp, m, n, ng, scale, C, ldc, qo, s);
-      if (!fa) return launch_11_tile<0, 1>(t, a_mant, a_exp, b_mant, b_exp, m, n, ng, scale, C, ldc, qo, s);
-      if (!fb) return launch_11_tile<1, 0>(t, a_mant, a_exp, b_mant, b_exp, m, n, ng, scale, C, ldc, qo, s);
-      return launch_11_tile<1, 1>(t, a_mant, a_exp, b_mant, b_exp, m, n, ng, scale, C, ldc, qo, s);
+hipError_t launch_tiled(const Product& p, const Output& o, int tile) {
+  if (tile == 1) return launch_tile<256, 128>(p, o);
+  if (tile == 2) return launch_tile<256, 64>(p, o);
+  if (tile == 3) return launch_tile<128, 64>(p, o);
+  if (tile == 4) return launch_tile<128, 128>(p, o);
+  if (p.na == 1 && p.nb == 1) return launch_fmt<1, 1, G>(p, o);
+  if (p.na == 1 && p.nb == 2) return launch_fmt<1, 2, G>(p, o);
+  if (p.na == 2 && p.nb == 1) return launch_fmt<2, 1, G>(p, o);
+  return launch_fmt<2, 2, G>(p, o);
+}
+
+template <int NA, int NB, int G>
+hipError_t launch_direct_fmt(const Product& p, const GemmPlan& plan, float* C, int64_t ldc, hipStream_t s) {
+#define FASTBFP_DIRECT(FA, FB)                                                                                    \
+  return launch_direct_t<NA, NB, FA, FB, G>(plan.rm, plan.rn, p.a_mant, p.a_exp, p.a_ps, p.b_mant, p.b_exp, p.b_ps, \
+                                            p.M, p.N, p.ng, p.scale, C, ldc, s)
+  if (!p.fa && !p.fb) FASTBFP_DIRECT(0, 0);
+  if (!p.fa) FASTBFP_DIRECT(0, 1);
+  if (!p.fb) FASTBFP_DIRECT(1, 0);
+  FASTBFP_DIRECT(1, 1);
+#undef FASTBFP_DIRECT
+}
+
+template <int G>
+hipError_t launch_direct(const Product& p, const GemmPlan& plan, float* C, int64_t ldc, hipStream_t s) {
+  if (p.na == 1 && p.nb == 1) return launch_direct_fmt<1, 1, G>(p, plan, C, ldc, s);
+  if (p.na == 1 && p.nb == 2) return launch_direct_fmt<1, 2, G>(p, plan, C, ldc, s);
+  if (p.na == 2 && p.nb == 1) return launch_direct_fmt<2, 1, G>(p, plan, C, ldc, s);
+  return launch_direct_fmt<2, 2, G>(p, plan, C, ldc, s);
+}
+
+int fmt_flag(int m, int planes) { return planes == 1 ? plane0_fp4(m) : m <= 6; }
+
+Product make_product(const uint8_t* a_mant, const uint8_t* a_exp, int a_m, int na, const uint8_t* b_mant,
+                     const uint8_t* b_exp, int b_m, int nb, int64_t M, int64_t N, int64_t K, int g, int scale_log2) {
+  return Product{a_mant, a_exp, M * (K / g) * plane_group_bytes(g, a_m, 0), b_mant, b_exp,
+                 N * (K / g) * plane_group_bytes(g, b_m, 0), (int)M, (int)N, (int)(K / 16), na, nb, fmt_flag(a_m, na),
+                 fmt_flag(b_m, nb), ldexpf(1.0f, scale_log2)};
+}
+
+int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+}  // namespace
+
+// The plan of a product that has a workspace.  A product whose tiles fill the
+// card runs as without one.  With fewer tiles, a tile's serial run of K slabs
+// sets the time (dW of ResNet-18's conv2_x, 576 x 64 x 802816, has 5 tiles of
+// 128 x 64 with 6272 slabs each: 3.9 ms), so the candidates below are priced
+// and the cheapest is taken: every tile with K in as many parts as fill one or
+// more workgroups per CU, and the few-output kernel.  Prices in us, from sweeps
+// of every tile x parts and of the few-output kernel's tiles over weight
+// gradients, few-token and small products on MI355X (measured, best of each):
+//   576 x 64 x 802816 (2,2)     3905 -> 84  (128x64 in 96 parts)
+//   2304 x 256 x 50176 (4,4)     263 -> 55  (256x256 in 28 parts)
+//   1024 x 4096 x 16384 (4,4)    126 -> 93  (256x256 in 4 parts)
+//   1024 x 1024 x 8192 (6,6)     134 -> 37  (256x128 in 8 parts)
+//   16 x 16384 x 4096 (4,4)       23 -> 17  (few-output, 32 x 32)
+//   1 x 4096 x 4096 (4,4)         17 -> 4.9 (few-output, 16 x 16)
+//   256 x 256 x 256 (4,4)        4.4 -> 2.6 (few-output, 16 x 16)
+//   2048 x 1024 x 4096 (4,4)    25.0, any split 30 or more: whole
+GemmPlan gemm_plan(int a_m, int na, int b_m, int nb, int64_t M, int64_t N, int64_t K, int g) {
+  const int fa = fmt_flag(a_m, na), fb = fmt_flag(b_m, nb);
+  const bool one = na == 1 && nb == 1 && g == 16;
+  const int rule = one ? gemm_mx11_tile(M, N, fa, false) : 0;
+  GemmPlan best{rule, 0, 1, 0, 0};
+  const int64_t slabs = ceil_div(K / 16, mx::KG);
+  if (slabs == 0 || M * N > (int64_t(1) << 25)) return best;  // (at least 512 tiles of 256 x 256)
+
+  // Tiles: rows, columns, and the time of one slab with 1 and with 2 workgroups
+  // on a CU (0: they do not fit), for FP6 and for FP4 codes on both sides.
+  struct Tile {
+    int id, bm, bn;
+    double us[2][2];
+  };
+  static const Tile kTiles[] = {{0, 256, 256, {{1.8, 0.0}, {1.45, 0.0}}},
+                                {1, 256, 128, {{1.2, 0.0}, {0.95, 1.35}}},
+                                {4, 128, 128, {{0.95, 1.3}, {0.68, 0.92}}},
+                                {3, 128, 64, {{0.72, 1.0}, {0.5, 0.7}}}};
+  // The default tile of the other operand formats (launch_mx_t), priced by the
+  // MFMAs of a wave and slab.
+  const bool wide22 = na == 2 && nb == 2 && fa && fb;
+  Tile def{0, (na == 1 || wide22) ? 256 : 128, nb == 1 ? 256 : 128, {}};
+  const int per_pair = g == 32 ? na * nb : 2 * (na == 2 && fa ? nb : nb == 2 && fb ? na : na * nb == 4 ? 3 : na * nb);
+  def.us[0][0] = def.us[1][0] = 0.6 + 0.0115 * (def.bm / 32) * (def.bn / 32) * per_pair;
+
+  double best_us = 1e30;
+  auto tile_us = [&](const Tile& t, int64_t parts, int64_t part_slabs) {
+    const double* us = t.us[one && fa && fb];
+    const int occ = us[1] > 0.0 ? 2 : 1;
+    const int64_t wgs = ceil_div(M, t.bm) * ceil_div(N, t.bn) * parts;
+    const int64_t full = wgs / (256 * occ), rest = wgs % (256 * occ);
+    const double slab = full * us[occ - 1] + (rest == 0 ? 0.0 : rest <= 256 ? us[0] : us[1]);
+    const double fix = 2.0 + 2.0 * (t.bm * t.bn) / 65536.0;  // a tile's start and its C
+    // a second launch, and every part's sums written and read
+    const double sum = parts > 1 ? 4.0 + 8e-6 / 5.0 * parts * M * N : 0.0;
+    return part_slabs * slab + fix * (full + (rest > 0)) + sum;
+  };
+  auto consider = [&](const Tile& t) {
+    const int64_t tiles = ceil_div(M, t.bm) * ceil_div(N, t.bn);
+    for (int fill = 0; fill <= 2; ++fill) {  // whole, or in parts that fill 256 or 512 workgroups
+      int64_t parts = fill == 0 ? 1 : 256 * fill / tiles;
+      parts = parts < slabs / 4 ? parts : slabs / 4;  // at least four slabs in each
+      if (fill > 0 && parts <= 1) continue;
+      int64_t ps = fill == 0 ? slabs : ceil_div(ceil_div(slabs, parts), 2) * 2;  // (exponents come in slab pairs)
+      parts = ceil_div(slabs, ps);
+      if (fill > 0 && (parts <= 1 || parts * M * gemm_plan_ld(N) * 4 > (int64_t(1) << 28))) continue;
+      const double us = tile_us(t, parts, ps);
+      if (us < 0.95 * best_us) {
+        best_us = us;
+        best = GemmPlan{t.id, parts > 1 ? (int)ps : 0, (int)parts, 0, 0};
+      }
+    }
+  };
+  if (one) {
+    for (const Tile& t : kTiles)  // the tile used without a workspace first: the others have to beat it
+      if (t.id == rule) consider(t);
+    for (const Tile& t : kTiles)
+      if (t.id != rule) consider(t);
+  } else {
+    consider(def);
+  }
+
+  // The few-output kernel: its operand reads (every workgroup reads its rows of
+  // both, 7 TB/s from L2 and the Infinity Cache) and the supersteps a wave waits
+  // for in turn (1.36, 2.8 and 4.2 us each on its three tiles, half of it hidden
+  // under the reads).  A tenth of margin: the tiled kernel's prices are the
+  // firmer ones.
+  const double va = (na == 1 && fa ? 0.5 : 0.75) + (na == 2 ? (fa ? 0.5 : 0.75) : 0.0) + 1.0 / g;
+  const double vb = (nb == 1 && fb ? 0.5 : 0.75) + (nb == 2 ? (fb ? 0.5 : 0.75) : 0.0) + 1.0 / g;
+  const int64_t nss = ceil_div(K, 256), per_wave = ceil_div(nss, direct::kMaxWaves);
+  double direct_us = 1e30;
+  static const struct { int rm, rn; double us; } kDirect[] = {{1, 1, 1.36}, {2, 2, 2.8}, {4, 2, 4.2}};
+  for (const auto& d : kDirect) {
+    const double tm = (double)ceil_div(M, 16 * d.rm), tn = (double)ceil_div(N, 16 * d.rn);
+    const double rows_a = M < 16 * d.rm ? M : 16 * d.rm, rows_b = N < 16 * d.rn ? N : 16 * d.rn;
+    const double us = 1.5 + tm * tn * K * (rows_a * va + rows_b * vb) / 7e6 + 0.5 * d.us * per_wave;
+    if (us < direct_us && us < 0.9 * best_us) {
+      direct_us = us;
+      best = GemmPlan{rule, 0, 1, d.rm, d.rn};
     }
   }
-  if (na == 1 && nb == 1)
-    return launch_fmt<1, 1, G>(fa, fb, a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, m, n, ng, scale, C, ldc, qo, s);
-  if (na == 1 && nb == 2)
-    return launch_fmt<1, 2, G>(fa, fb, a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, m, n, ng, scale, C, ldc, qo, s);
-  if (na == 2 && nb == 1)
-    return launch_fmt<2, 1, G>(fa, fb, a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, m, n, ng, scale, C, ldc, qo, s);
-  return launch_fmt<2, 2, G>(fa, fb, a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, m, n, ng, scale, C, ldc, qo, s);
+  return best;
 }
 
-static hipError_t launch_gemm_any(const uint8_t* a_mant, const uint8_t* a_exp, int a_m, int na, const uint8_t* b_mant,
-                                  const uint8_t* b_exp, int b_m, int nb, int64_t M, int64_t N, int64_t K, int g,
-                                  int scale_log2, float* C, int64_t ldc, const OutBFP* qo, int tile,
-                                  hipStream_t s) {
-  if (g == 32)
-    return launch_gemm_g<32>(a_mant, a_exp, a_m, na, b_mant, b_exp, b_m, nb, M, N, K, scale_log2, C, ldc, qo, 0, s);
-  return launch_gemm_g<16>(a_mant, a_exp, a_m, na, b_mant, b_exp, b_m, nb, M, N, K, scale_log2, C, ldc, qo, tile, s);
-}
+int64_t gemm_plan_ld(int64_t N) { return (N + 3) / 4 * 4; }
 
 hipError_t launch_gemm_mx(const uint8_t* a_mant, const uint8_t* a_exp, int a_m, int na, const uint8_t* b_mant,
                           const uint8_t* b_exp, int b_m, int nb, int64_t M, int64_t N, int64_t K, int g,
                           int scale_log2, float* C, int64_t ldc, int tile, hipStream_t s) {
-  return launch_gemm_any(a_mant, a_exp, a_m, na, b_mant, b_exp, b_m, nb, M, N, K, g, scale_log2, C, ldc, nullptr, tile,
-                         s);
+  if (M == 0 || N == 0) return hipSuccess;
+  const Product p = make_product(a_mant, a_exp, a_m, na, b_mant, b_exp, b_m, nb, M, N, K, g, scale_log2);
+  const Output o{C, ldc, nullptr, 0, s};
+  if (g == 32) return launch_tiled<32>(p, o, 0);
+  if (tile < 0) tile = na == 1 && nb == 1 ? gemm_mx11_tile(M, N, p.fa, false) : 0;
+  return launch_tiled<16>(p, o, tile);
 }
 
 hipError_t launch_gemm_mx_bfp(const uint8_t* a_mant, const uint8_t* a_exp, int a_m, int na, const uint8_t* b_mant,
                               const uint8_t* b_exp, int b_m, int nb, int64_t M, int64_t N, int64_t K, int g,
                               int scale_log2, int c_m, int mode, uint64_t seed, uint8_t* c_mant, uint8_t* c_exp,
                               uint32_t* status, hipStream_t s) {
+  if (M == 0 || N == 0) return hipSuccess;
   const OutBFP qo{c_mant, c_mant + M * (N / 16) * plane_group_bytes(16, c_m, 0), c_exp, status, c_m, mode,
                   c_m <= 4 ? plane0_fp4(c_m) : c_m <= 6, (uint32_t)seed, (uint32_t)(seed >> 32)};
-  return launch_gemm_any(a_mant, a_exp, a_m, na, b_mant, b_exp, b_m, nb, M, N, K, g, scale_log2, nullptr, N, &qo, -1, s);
+  const Product p = make_product(a_mant, a_exp, a_m, na, b_mant, b_exp, b_m, nb, M, N, K, g, scale_log2);
+  const Output o{nullptr, N, &qo, 0, s};
+  if (g == 32) return launch_tiled<32>(p, o, 0);
+  return launch_tiled<16>(p, o, na == 1 && nb == 1 ? gemm_mx11_tile(M, N, p.fa, true) : 0);
+}
+
+hipError_t launch_gemm_plan(const GemmPlan& plan, const uint8_t* a_mant, const uint8_t* a_exp, int a_m, int na,
+                            const uint8_t* b_mant, const uint8_t* b_exp, int b_m, int nb, int64_t M, int64_t N,
+                            int64_t K, int g, int scale_log2, float* C, int64_t ldc, hipStream_t s) {
+  if (M == 0 || N == 0) return hipSuccess;
+  const Product p = make_product(a_mant, a_exp, a_m, na, b_mant, b_exp, b_m, nb, M, N, K, g, scale_log2);
+  if (plan.rm > 0) return g == 32 ? launch_direct<32>(p, plan, C, ldc, s) : launch_direct<16>(p, plan, C, ldc, s);
+  const Output o{C, ldc, nullptr, plan.parts > 1 ? plan.part_slabs : 0, s};
+  return g == 32 ? launch_tiled<32>(p, o, 0) : launch_tiled<16>(p, o, plan.tile);
 }
 
 }  // namespace fastbfp

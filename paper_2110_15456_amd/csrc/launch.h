@@ -104,6 +104,28 @@ hipError_t launch_gemm_mx_bfp(const uint8_t* a_mant, const uint8_t* a_exp, int a
                               int scale_log2,
                               int c_m, int mode, uint64_t seed, uint8_t* c_mant, uint8_t* c_exp, uint32_t* status,
                               hipStream_t s);
+// How a product with a workspace runs.  rm, rn > 0: the few-output kernel on
+// tiles of 16 rm x 16 rn (gemm_direct.h); otherwise the tiled kernel on `tile`,
+// with K in `parts` parts of `part_slabs` slabs (parts > 1: each part's sums go
+// to its own FP32 matrix in the workspace, added up afterwards).  The plan
+// fixes the order in which a product's terms are summed, so FP32 and converted
+// output use the same one.
+struct GemmPlan {
+  int tile, part_slabs, parts, rm, rn;
+};
+GemmPlan gemm_plan(int a_m, int na, int b_m, int nb, int64_t M, int64_t N, int64_t K, int g);
+// Row stride of a part's matrix of N columns.
+int64_t gemm_plan_ld(int64_t N);
+// The product as planned: C (row stride ldc) is the result, or with parts > 1
+// the parts' matrices, M * ldc values each.
+hipError_t launch_gemm_plan(const GemmPlan& plan, const uint8_t* a_mant, const uint8_t* a_exp, int a_m, int na,
+                            const uint8_t* b_mant, const uint8_t* b_exp, int b_m, int nb, int64_t M, int64_t N,
+                            int64_t K, int g, int scale_log2, float* C, int64_t ldc, hipStream_t s);
+// C = the sum of the `parts` M x N matrices at p (rows gemm_plan_ld(N) apart),
+// in a fixed order; or that sum converted as launch_gemm_mx_bfp converts C.
+hipError_t launch_parts_sum(const float* p, int parts, int64_t M, int64_t N, float* C, int64_t ldc, hipStream_t s);
+hipError_t launch_parts_convert(const float* p, int parts, int64_t M, int64_t N, int c_m, int mode, uint64_t seed,
+                                uint8_t* c_mant, uint8_t* c_exp, uint32_t* status, hipStream_t s);
 // The general BFP GEMM (gemm_general.hip): any m_a <= a_m and m_b <= b_m, g in
 // {4, 8, 16, 32, 64} (K a multiple of g and of 16).  With P non-null it writes
 // the int32 group partials P[K/g][M][N] instead of C.

@@ -1,0 +1,130 @@
+"""The routes a product takes from its shape (bfp_gemm_ws): the few-output
+kernel and K taken in parts, each against the oracle under the GEMM's tolerance
+(|C_gpu - C_oracle| <= 1e-6 * sum_G |T_G|) and beside the tiled kernel in one
+run over K, and the converted output against converting the FP32 one."""
+from __future__ import annotations
+
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2110_15456_amd as fb
+from paper_2110_15456_amd import _lib, synth
+from gpu_util import announce, chunk_drops, THREADS
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-6
+MODES = ("nearest", "stochastic", "truncate")
+
+
+def make(M, N, K, g, m_a, m_b, seed):
+    a = synth.draw("half_normal", (M, K), seed)
+    b = synth.draw("grads", (N, K), seed + 1)
+    A, B = (fb.quantize(torch.from_numpy(x).cuda(), g=g, m=m) for x, m in ((a, m_a), (b, m_b)))
+    oa, ob = (oracle.quantize(x, g=g, m=m)[:2] for x, m in ((a, m_a), (b, m_b)))
+    return A, B, oa, ob
+
+
+def against_oracle(C, A, B, oa, ob, m_a, m_b):
+    Co, S = oracle.gemm(oa[0], oa[1], A.m, ob[0], ob[1], B.m, g=A.g, m_a=m_a, m_b=m_b, threads=THREADS)
+    err = np.abs(C.cpu().numpy().astype(np.float64) - Co)
+    assert np.all(err <= TOL * S), "max err/sum|T| = %.3g" % float((err / np.maximum(S, 1e-300)).max())
+
+
+def full_size(A, B):
+    nb = ctypes.c_size_t(0)
+    assert _lib.load().bfp_gemm_ws_full_size(A.m, B.m, A.rows, B.rows, A.len, A.g, A.m, B.m, 0, ctypes.byref(nb)) == 0
+    return nb.value
+
+
+# tile edges of 16, 32 and 64 rows, odd column counts, one unit of K to ragged
+# supersteps (16 units) and more supersteps than waves
+@pytest.mark.parametrize("g", [16, 32])
+@pytest.mark.parametrize("shape", [(1, 40, 32), (17, 33, 288), (31, 161, 1056), (65, 150, 2592), (3, 65, 4640)])
+def test_few_outputs(g, shape):
+    M, N, K = shape
+    for m_a in (2, 4, 6, 8):
+        for m_b in (2, 4, 6, 8):
+            A, B, oa, ob = make(M, N, K, g, m_a, m_b, 7000 + M + 8 * m_a + m_b)
+            for u_a in chunk_drops(m_a):
+                for u_b in chunk_drops(m_b):
+                    announce("few outputs %dx%dx%d g=%d stored (%d,%d) at (%d,%d)" % (M, N, K, g, m_a, m_b, u_a, u_b))
+                    against_oracle(fb.gemm(A, B, u_a, u_b), A, B, oa, ob, u_a, u_b)
+                    against_oracle(fb.gemm(A, B, u_a, u_b, workspace=False), A, B, oa, ob, u_a, u_b)
+
+
+# K in parts: every plane count, full and ragged slabs, parts of unequal length,
+# few and many parts (both orders of the sum), columns not a multiple of 4
+@pytest.mark.parametrize("g", [16, 32])
+@pytest.mark.parametrize("mm", [(2, 2), (4, 4), (4, 2), (6, 6), (4, 6), (8, 6), (8, 8)])
+@pytest.mark.parametrize("shape", [(300, 270, 16384), (300, 270, 16384 + 96), (272, 259, 65536), (520, 1030, 8192)])
+def test_parts(g, mm, shape):
+    M, N, K = shape
+    m_a, m_b = mm
+    announce("parts %dx%dx%d g=%d (%d,%d)" % (M, N, K, g, m_a, m_b))
+    A, B, oa, ob = make(M, N, K, g, m_a, m_b, 7100 + M + N + m_a * 10 + m_b)
+    assert full_size(A, B) > 0 and fb.gemm_ws_size(A, B) == 0
+    C = fb.gemm(A, B)
+    idx = np.arange(0, M, 7)
+    Co, S = oracle.gemm(oa[0], oa[1], m_a, ob[0], ob[1], m_b, g=g, m_a=m_a, m_b=m_b, rows=idx, threads=THREADS)
+    err = np.abs(C.cpu().numpy().astype(np.float64)[idx] - Co)
+    assert np.all(err <= TOL * S)
+    # the same bits on every run
+    out = torch.empty((M, N), device="cuda")
+    for _ in range(3):
+        out.fill_(float("nan"))
+        assert torch.equal(fb.gemm(A, B, out=out), C)
+    # without the room for the parts' sums: in one run over K
+    W = fb.gemm(A, B, workspace=torch.empty(256, dtype=torch.uint8, device="cuda"))
+    assert torch.equal(W, fb.gemm(A, B, workspace=False))
+
+
+@pytest.mark.parametrize("mm", [(4, 4), (6, 4), (2, 8)])
+@pytest.mark.parametrize("shape", [(33, 80, 1040), (300, 272, 16384), (144, 64, 90112)])
+def test_converted_output(mm, shape):
+    M, N, K = shape
+    A, B, _, _ = make(M, N, K, 16, mm[0], mm[1], 7300 + M)
+    C = fb.gemm(A, B)
+    for c_m in (2, 4, 6, 8):
+        for mode in MODES:
+            announce("converted %dx%dx%d (%d,%d) -> %d %s" % (M, N, K, mm[0], mm[1], c_m, mode))
+            st = torch.zeros(1, dtype=torch.int32, device="cuda")
+            T = fb.gemm_bfp(A, B, c_m, rounding=mode, seed=31, status=st)
+            R = fb.quantize(C, g=16, m=c_m, rounding=mode, seed=31)
+            assert torch.equal(T.exp, R.exp) and torch.equal(T.mant, R.mant) and int(st.item()) == 0
+
+
+def test_lowered_and_regrouped_operands():
+    """Repacked operands (groups of 8 and 64, a precision between chunk
+    boundaries) in parts and on the few-output kernel."""
+    for (M, N, K) in ((20, 48, 1024), (260, 200, 32768)):
+        for g, m, use in ((8, 4, 4), (64, 4, 4), (16, 4, 2), (16, 6, 3)):
+            announce("repacked %dx%dx%d g=%d m=%d at %d" % (M, N, K, g, m, use))
+            A, B, oa, ob = make(M, N, K, g, m, m, 7400 + g)
+            against_oracle(fb.gemm(A, B, use, use), A, B, oa, ob, use, use)
+
+
+def test_captured():
+    """The routes under graph capture: replays give the eager result."""
+    for (M, N, K) in ((16, 256, 2048), (300, 270, 16384)):
+        announce("captured %dx%dx%d" % (M, N, K))
+        A, B, _, _ = make(M, N, K, 16, 4, 4, 7500)
+        want = fb.gemm(A, B).clone()
+        out = torch.empty((M, N), device="cuda")
+        s = torch.cuda.Stream()
+        s.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(s):
+            fb.gemm(A, B, out=out)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            fb.gemm(A, B, out=out)
+        for _ in range(4):
+            out.fill_(float("nan"))
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want)
