@@ -183,6 +183,16 @@ __global__ __launch_bounds__(256) void k_quantize_rows(const float* __restrict__
   }
 }
 
+// Unit rows per wave of k_quantize_cols.  Two: short blocks (128 to 512 values
+// of a column, 6 to 50 KB of LDS gather) fill the card on small tensors and
+// keep several blocks on a CU.  Eight, whose gather took up to 100 KB and left
+// one block per CU, took 64 us on 24 x 1056 x 777 (g = 32, m = 6; now 33), 132
+// us on 8192^2 (g = 32, m = 8, stochastic; now 83) and 13 us on 1024^2 (now 5);
+// 8192^2 at g = 16, m = 4 is within 1% (65 us, 5.0 TB/s).  One row gains up to
+// 1 us more on 1024^2 and loses 2-6% on large ones.  The adaptive path keeps
+// eight: its partial sums are counted by them (adaptive_parts).
+constexpr int cols_ngt(bool adapt) { return adapt ? 8 : 2; }
+
 // Groups down the columns of x[R][C] (transpose-on-quantize).  Output row c is
 // column c of x; its group j covers x[j*G .. j*G+G-1][c] and has
 // gid = c * (R/G) + j.  A block takes 64 columns (one per lane: every load
@@ -269,60 +279,81 @@ __global__ __launch_bounds__(256) void k_quantize_cols(const float* __restrict__
   if (status && any_bad) atomicOr(status, 1u);
 }
 
-// BFP -> FP32: y = +-q * 2^(E-127-(m-1)).  One lane per U = max(G, 16)
-// values (a 16-value unit of groups of 4 or 8, or one group).  P0 / P1: the
-// plane formats (launch.h); with two planes q = c0 * 2^s + c1, s = 2 when
-// plane 1 is a Lo2 plane and 4 otherwise (both chunks carry the sign).
-template <int G, int NCH, int P0, int P1>
-__global__ __launch_bounds__(256) void k_dequantize(const uint8_t* __restrict__ mant, const uint8_t* __restrict__ exps,
-                                                    int64_t nunits, int m, float* __restrict__ y) {
-  constexpr int U = G < 16 ? 16 : G, NGU = U / G;
-  const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (u >= nunits) return;
-  constexpr int PK[2] = {P0, P1};
-  constexpr int B0 = P0 != kPlaneFP6 ? U / 2 : U * 3 / 4;  // bytes per unit in plane 0
-  uint32_t w[NCH][U * 6 / 32];
+// The 24 bits of FP6 codes of values 4k .. 4k + 3 of a 16-value unit.
+__device__ __forceinline__ uint32_t fp6_quad(const uint8_t* unit, int k) {
+  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+  const u2 d = stream_load(reinterpret_cast<const u2*>(unit + (k < 2 ? 0 : 4)));
+  return (uint32_t)((((uint64_t)d.y << 32) | d.x) >> (k < 2 ? 24 * k : 24 * k - 32));
+}
+
+// The four signed chunks of quad k (values 4k .. 4k + 3) of the unit at `unit`
+// in a plane of kind KIND.
+template <int KIND>
+__device__ __forceinline__ void decode_quad(const uint8_t* unit, int k, int (&c)[4]) {
+  if constexpr (KIND == kPlaneFP4) {
+    const uint32_t x = stream_load(reinterpret_cast<const uint16_t*>(unit + 2 * k));
 #pragma unroll
-  for (int p = 0; p < NCH; ++p) {
-    const int gb = PK[p] != kPlaneFP6 ? U / 2 : U * 3 / 4;
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(mant + p * nunits * B0 + u * gb);
+    for (int t = 0; t < 4; ++t) {
+      const int mag = (int)((x >> (4 * t)) & 7u);
+      c[t] = (x >> (4 * t)) & 8u ? -mag : mag;
+    }
+  } else {
+    uint32_t w;
+    if constexpr (KIND == kPlaneLo2) {
+      typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+      const u2 d = stream_load(reinterpret_cast<const u2*>(unit));
+      uint32_t t0, t1, t2;
+      lo2_unpack(d.x, d.y, t0, t1, t2);
+      const uint32_t lo = k < 2 ? t0 : t1, hi = k < 2 ? t1 : t2;
+      w = (uint32_t)((((uint64_t)hi << 32) | lo) >> (k < 2 ? 24 * k : 24 * k - 32));
+    } else {
+      w = fp6_quad(unit, k);
+    }
 #pragma unroll
-    for (int i = 0; i < U * 6 / 32; ++i) w[p][i] = i < gb / 4 ? src[i] : 0u;
-    if (PK[p] == kPlaneLo2) {
-      // back to three FP6 code dwords per 16 values (last half first: in place)
-#pragma unroll
-      for (int h = U / 16 - 1; h >= 0; --h) {
-        uint32_t t0, t1, t2;
-        lo2_unpack(w[p][2 * h], w[p][2 * h + 1], t0, t1, t2);
-        w[p][3 * h] = t0;
-        w[p][3 * h + 1] = t1;
-        w[p][3 * h + 2] = t2;
-      }
+    for (int t = 0; t < 4; ++t) {
+      const uint32_t code = (w >> (6 * t)) & 0x3Fu;
+      c[t] = KIND == kPlaneLo2 ? e2m3_eighth_decode(code) : e2m3_half_decode(code);
     }
   }
-  int e[NGU];
+}
+
+// BFP -> FP32: y = +-q * 2^(E-127-(m-1)).  Bound by its stores (4 of every 4.6
+// to 5.6 bytes), so a lane takes four consecutive values and a wave's store
+// instruction writes 1 KB of y in one piece: a lane per 16-value unit, which
+// stores 64 bytes in four pieces 64 bytes apart from its neighbours', took 95
+// us on 64M values of m = 4, g = 16 (3.4 TB/s) and 157 at g = 64; now 59 and 58
+// (5.5 TB/s).  kDeqQuads quads per lane keep that many loads in
+// flight.  P0 / P1: the plane formats (launch.h); with two planes q = c0 * 2^s
+// + c1, s = 2 when plane 1 is a Lo2 plane and 4 otherwise (both chunks carry
+// the sign).  gsh: log2 of the quads in a group.
+constexpr int kDeqQuads = 4;
+template <int NCH, int P0, int P1>
+__global__ __launch_bounds__(256) void k_dequantize(const uint8_t* __restrict__ mant, const uint8_t* __restrict__ exps,
+                                                    int64_t nquads, int gsh, int m, float* __restrict__ y) {
+  constexpr int B0 = P0 != kPlaneFP6 ? 8 : 12, B1 = P1 != kPlaneFP6 ? 8 : 12;  // bytes per unit
+  const int64_t q0 = (int64_t)blockIdx.x * (256 * kDeqQuads) + threadIdx.x;
+  const uint8_t* mant1 = mant + nquads / 4 * B0;
+  int c[kDeqQuads][4], e[kDeqQuads];
 #pragma unroll
-  for (int k = 0; k < NGU; ++k) e[k] = (int)exps[u * NGU + k] - 127 - (m - 1);
-  auto chunk = [&](int p, int t) {
-    if (PK[p] == kPlaneFP4) {
-      const uint32_t nib = (w[p][t >> 3] >> (4 * (t & 7))) & 0xFu;
-      return (nib & 8u) ? -(int)(nib & 7u) : (int)(nib & 7u);
+  for (int i = 0; i < kDeqQuads; ++i) {
+    const int64_t q = min(q0 + 256 * i, nquads - 1);  // (quads past the end reread the last one)
+    const int k = (int)(q & 3);
+    decode_quad<P0>(mant + (q >> 2) * B0, k, c[i]);
+    if constexpr (NCH == 2) {
+      int lo[4];
+      decode_quad<P1>(mant1 + (q >> 2) * B1, k, lo);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) c[i][t] = c[i][t] * (P1 == kPlaneLo2 ? 4 : 16) + lo[t];
     }
-    if (PK[p] == kPlaneLo2) return e2m3_eighth_decode(fp6_field(w[p], t));
-    return e2m3_half_decode(fp6_field(w[p], t));
-  };
-  float4* dst = reinterpret_cast<float4*>(y + u * U);
+    e[i] = (int)exps[q >> gsh] - 127 - (m - 1);
+  }
+  typedef float f4 __attribute__((ext_vector_type(4)));
 #pragma unroll
-  for (int i = 0; i < U / 4; ++i) {
-    float v[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int t = 4 * i + k;
-      int q = chunk(0, t);
-      if (NCH == 2) q = q * (P1 == kPlaneLo2 ? 4 : 16) + chunk(NCH - 1, t);
-      v[k] = ldexpf((float)q, e[t / G]);
-    }
-    dst[i] = make_float4(v[0], v[1], v[2], v[3]);
+  for (int i = 0; i < kDeqQuads; ++i) {
+    const int64_t q = q0 + 256 * i;
+    if (q < nquads)
+      stream_store(reinterpret_cast<f4*>(y) + q, f4{ldexpf((float)c[i][0], e[i]), ldexpf((float)c[i][1], e[i]),
+                                                    ldexpf((float)c[i][2], e[i]), ldexpf((float)c[i][3], e[i])});
   }
 }
 
@@ -340,7 +371,7 @@ template <int G, int MODE, int NCH, int P0, bool ADAPT = false, int P1 = kPlaneF
 static hipError_t launch_cols_t(const float* x, int64_t R, int64_t C, int m, uint64_t seed, uint8_t* mant0,
                                 uint8_t* mant1, uint8_t* exps, uint32_t* status, double* part, hipStream_t s,
                                 int64_t nbatch = 1) {
-  constexpr int NGT = G == 64 ? 2 : 8;  // (the LDS gather holds 4 * NGT units of 64 columns)
+  constexpr int NGT = cols_ngt(ADAPT);
   const int64_t upr = R / (G < 16 ? 16 : G);  // units per output row (as in the kernel)
   const int64_t nbx = (C + 63) / 64, nby = (upr + 4 * NGT - 1) / (4 * NGT);
   const int64_t nbxy = nbx * nby;
@@ -395,7 +426,7 @@ int64_t quantize_rows_blocks(int64_t rows, int64_t len, int g) {
 }
 
 int64_t quantize_cols_blocks(int64_t R, int64_t C, int g, int64_t nbatch) {
-  const int64_t U = g < 16 ? 16 : g, NGT = g == 64 ? 2 : 8;
+  const int64_t U = g < 16 ? 16 : g, NGT = cols_ngt(false);
   return ((C + 63) / 64) * ((R / U + 4 * NGT - 1) / (4 * NGT)) * nbatch;
 }
 
@@ -662,35 +693,23 @@ hipError_t launch_weight_update(const float* w, const float* dw, float alpha, fl
   return launch_dual_any<true>(w, dw, alpha, w_out, R, C, m, mode, seed_r, seed_c, mr, er, mc, ec, status, s);
 }
 
-template <int G, int NCH, int P0, int P1 = kPlaneFP6>
-static hipError_t launch_deq_t(const uint8_t* mant, const uint8_t* exps, int64_t ngroups, int m, float* y,
+template <int NCH, int P0, int P1 = kPlaneFP6>
+static hipError_t launch_deq_t(const uint8_t* mant, const uint8_t* exps, int64_t nquads, int gsh, int m, float* y,
                                hipStream_t s) {
-  const int64_t nunits = G < 16 ? ngroups * G / 16 : ngroups;
-  const unsigned blocks = (unsigned)((nunits + 255) / 256);
-  hipLaunchKernelGGL((k_dequantize<G, NCH, P0, P1>), dim3(blocks), dim3(256), 0, s, mant, exps, nunits, m, y);
+  const unsigned blocks = (unsigned)((nquads + 256 * kDeqQuads - 1) / (256 * kDeqQuads));
+  hipLaunchKernelGGL((k_dequantize<NCH, P0, P1>), dim3(blocks), dim3(256), 0, s, mant, exps, nquads, gsh, m, y);
   return hipGetLastError();
-}
-
-template <int G>
-static hipError_t launch_deq_g(const uint8_t* mant, const uint8_t* exps, int64_t ngroups, int m, float* y,
-                               hipStream_t s) {
-  if (m <= 2) return launch_deq_t<G, 1, kPlaneFP4>(mant, exps, ngroups, m, y, s);
-  if (m <= 4) return launch_deq_t<G, 1, kPlaneFP6>(mant, exps, ngroups, m, y, s);
-  if (m <= 6) return launch_deq_t<G, 2, kPlaneFP6, kPlaneLo2>(mant, exps, ngroups, m, y, s);
-  return launch_deq_t<G, 2, kPlaneFP6, kPlaneFP6>(mant, exps, ngroups, m, y, s);
 }
 
 hipError_t launch_dequantize(const uint8_t* mant, const uint8_t* exps, int64_t rows, int64_t len, int g, int m,
                              float* y, hipStream_t s) {
-  const int64_t ngroups = rows * (len / g);
-  if (ngroups == 0) return hipSuccess;
-  switch (g) {
-    case 4: return launch_deq_g<4>(mant, exps, ngroups, m, y, s);
-    case 8: return launch_deq_g<8>(mant, exps, ngroups, m, y, s);
-    case 16: return launch_deq_g<16>(mant, exps, ngroups, m, y, s);
-    case 32: return launch_deq_g<32>(mant, exps, ngroups, m, y, s);
-    default: return launch_deq_g<64>(mant, exps, ngroups, m, y, s);
-  }
+  const int64_t nquads = rows * (len / 4);
+  if (nquads == 0) return hipSuccess;
+  const int gsh = g == 4 ? 0 : g == 8 ? 1 : g == 16 ? 2 : g == 32 ? 3 : 4;
+  if (m <= 2) return launch_deq_t<1, kPlaneFP4>(mant, exps, nquads, gsh, m, y, s);
+  if (m <= 4) return launch_deq_t<1, kPlaneFP6>(mant, exps, nquads, gsh, m, y, s);
+  if (m <= 6) return launch_deq_t<2, kPlaneFP6, kPlaneLo2>(mant, exps, nquads, gsh, m, y, s);
+  return launch_deq_t<2, kPlaneFP6, kPlaneFP6>(mant, exps, nquads, gsh, m, y, s);
 }
 
 }  // namespace fastbfp
