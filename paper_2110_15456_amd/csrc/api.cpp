@@ -95,6 +95,7 @@ size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
 // the workspace the repacked operands take (A's mantissas and exponents, then
 // B's, each 256-byte aligned).
 struct WsPlan {
+  int g_in;
   bool rep_a, rep_b;
   int64_t k_out;
   int g_out;
@@ -105,6 +106,7 @@ int ws_plan(int a_m, int b_m, int64_t M, int64_t N, int64_t K, int g, int m_a, i
   if (packed != 0 && packed != 1) return BFP_E_ARG;
   if (packed && g != 16) return BFP_E_UNSUPPORTED;
   const bool native = g == 16 || g == 32;
+  p->g_in = packed ? 16 : g;
   p->rep_a = packed || !native || planes_used(a_m, m_a) == 0;
   p->rep_b = packed || !native || planes_used(b_m, m_b) == 0;
   fastbfp::repack_shape(K, g, &p->k_out, &p->g_out);
@@ -440,7 +442,9 @@ int bfp_gemm_ws_size(int a_m_bits, int b_m_bits, int64_t M, int64_t N, int64_t K
 // The plan of a product through bfp_gemm_ws: on the operands as the kernel will
 // read them.
 static fastbfp::GemmPlan plan_of(const WsPlan& p, int a_m, int b_m, int64_t M, int64_t N, int m_a, int m_b) {
-  const int sa = p.rep_a ? m_a : a_m, sb = p.rep_b ? m_b : b_m;  // stored widths the kernel sees
+  // stored widths the kernel sees (groups of 64 keep their planes where they can)
+  const int sa = p.rep_a && !(p.g_in == 64 && planes_used(a_m, m_a)) ? m_a : a_m;
+  const int sb = p.rep_b && !(p.g_in == 64 && planes_used(b_m, m_b)) ? m_b : b_m;
   return fastbfp::gemm_plan(sa, planes_used(sa, m_a), sb, planes_used(sb, m_b), M, N, p.k_out, p.g_out);
 }
 
@@ -477,7 +481,18 @@ int bfp_gemm_ws(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, const
   const uint8_t *am = a_mant, *ae = a_exp, *bm = b_mant, *be = b_exp;
   int a_m = a_m_bits, b_m = b_m_bits;
   // (with K = 0 nothing is repacked or read: the kernel writes zeros)
-  if (p.rep_a) {
+  // (groups of 64 at the stored width or without the low chunk plane: the
+  // planes are those of groups of 32, only the exponents are doubled)
+  const bool twice = !packed && g == 64;
+  const bool twice_a = twice && planes_used(a_m_bits, m_a) != 0, twice_b = twice && planes_used(b_m_bits, m_b) != 0;
+  if (p.rep_a && twice_a) {
+    if (K > 0) {
+      uint8_t* oe = ws + align256(p.a_mant);
+      st = status_of(fastbfp::launch_exps_twice(a_exp, M * (K / 64), oe, s));
+      if (st != BFP_OK) return st;
+      ae = oe;
+    }
+  } else if (p.rep_a) {
     a_m = m_a;
     if (K > 0) {
       uint8_t *om = ws, *oe = ws + align256(p.a_mant);
@@ -486,7 +501,14 @@ int bfp_gemm_ws(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, const
       am = om, ae = oe;
     }
   }
-  if (p.rep_b) {
+  if (p.rep_b && twice_b) {
+    if (K > 0) {
+      uint8_t* oe = ws + align256(p.a_mant) + align256(p.a_exp) + align256(p.b_mant);
+      st = status_of(fastbfp::launch_exps_twice(b_exp, N * (K / 64), oe, s));
+      if (st != BFP_OK) return st;
+      be = oe;
+    }
+  } else if (p.rep_b) {
     b_m = m_b;
     if (K > 0) {
       uint8_t *om = ws + align256(p.a_mant) + align256(p.a_exp), *oe = om + align256(p.b_mant);

@@ -136,6 +136,9 @@ hipError_t launch_parts_convert(const float* p, int parts, int64_t M, int64_t N,
 void repack_shape(int64_t len, int g, int64_t* len_out, int* g_out);
 hipError_t launch_repack(const uint8_t* mant, const uint8_t* exps, int64_t rows, int64_t len, int g, int m, int m_use,
                          bool packed, uint8_t* out_mant, uint8_t* out_exps, hipStream_t s);
+// out[2 i] = out[2 i + 1] = exps[i]: the exponents of n groups of 64 for the
+// same values in groups of 32.
+hipError_t launch_exps_twice(const uint8_t* exps, int64_t n, uint8_t* out, hipStream_t s);
 hipError_t launch_gemm_general(const uint8_t* a_mant, const uint8_t* a_exp, int a_m, int m_a, const uint8_t* b_mant,
                                const uint8_t* b_exp, int b_m, int m_b, int64_t M, int64_t N, int64_t K, int g,
                                float* C, int64_t ldc, int32_t* P, hipStream_t s, bool packed = false);

@@ -21,20 +21,21 @@ namespace {
 
 __global__ void k_packed_header_clear(uint32_t* hdr) { *hdr = 0u; }
 
-// hdr = max(hdr, the largest exponent field of x[0 .. 4 n4)): kExpMaxGranules
-// 16-byte granules per block, in rounds of four independent loads per thread.
-// The word only grows, so a block whose maximum is not above the value it
-// reads skips its atomic.
-constexpr int kExpMaxGranules = 4096;
-__global__ __launch_bounds__(256) void k_exponent_max(const u32x4* __restrict__ x, int64_t n4, uint32_t* hdr) {
-  const int64_t i0 = (int64_t)blockIdx.x * kExpMaxGranules + threadIdx.x;
+// hdr = max(hdr, the largest exponent field of x[0 .. 4 n4)).  At most
+// kExpMaxBlocks blocks, each a contiguous run of rounds of 1024 16-byte granules
+// (four independent loads per thread and round).  Two blocks a CU: with 2048
+// blocks (64 KB each) the conversion of 8192 x 4096 at m = 4 took 74 us, with
+// 1024 62, 512 57, 256 66 (and 62, 58, 60 with 1024-thread blocks at 512, 256,
+// 128); on 2048^2 25 us with 1024 blocks, 16 with 512 or 256.
+constexpr int kExpMaxBlocks = 512;
+__global__ __launch_bounds__(256) void k_exponent_max(const u32x4* __restrict__ x, int64_t n4, int64_t rounds,
+                                                      uint32_t* hdr) {
   uint32_t e = 0;
-#pragma unroll
-  for (int r = 0; r < kExpMaxGranules / 1024; ++r) {
+  for (int64_t r = blockIdx.x * rounds; r < (blockIdx.x + 1) * rounds; ++r) {
     u32x4 v[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int64_t i = i0 + 1024 * r + 256 * j;
+      const int64_t i = 1024 * r + 256 * j + threadIdx.x;
       v[j] = i < n4 ? stream_load(x + i) : u32x4{0u, 0u, 0u, 0u};
     }
 #pragma unroll
@@ -102,25 +103,33 @@ __global__ __launch_bounds__(256) void k_quantize_packed(const float* __restrict
     // (b)-(d) the magnitudes, split into 2-bit chunks with the sign
     const int align = magnitude_align<MODE>(m, E);
     const uint32_t qmax = (1u << m) - 1u;
-    uint64_t plane[NP];
+    // Fields of values 0..7 and 8..15 of every plane, and the signs at bit 2 of
+    // each field; a field takes its sign only if its chunk is nonzero.  (The
+    // kernel is bound by this arithmetic beside its reads: with each field
+    // made and shifted into 64 bits by itself the conversion of 8192^2 at m = 4
+    // took 116 us, now 108.)
+    uint32_t plane[NP][2], sgn[2] = {0u, 0u};
 #pragma unroll
-    for (int c = 0; c < NP; ++c) plane[c] = 0;
+    for (int c = 0; c < NP; ++c) plane[c][0] = plane[c][1] = 0u;
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
       const uint32_t q = value_magnitude<MODE, true>(b[t], align, noise[t >> 2], t, qmax);
-      const uint32_t sgn = (b[t] >> 29) & 4u;  // the sign at bit 2 of a field
+      const int h = t >> 3, sh = 3 * (t & 7);
+      sgn[h] |= (b[t] >> 31) << (sh + 2);
 #pragma unroll
-      for (int c = 0; c < NP; ++c) {
-        const uint32_t ch = (q >> (2 * (NP - 1 - c))) & 3u;
-        plane[c] |= (uint64_t)(ch ? (sgn | ch) : 0u) << (3 * t);
-      }
+      for (int c = 0; c < NP; ++c) plane[c][h] |= ((q >> (2 * (NP - 1 - c))) & 3u) << sh;
     }
 #pragma unroll
     for (int c = 0; c < NP; ++c) {
       uint16_t* dst = reinterpret_cast<uint16_t*>(mant + (c * ngroups + gid) * 6);
-      dst[0] = (uint16_t)plane[c];
-      dst[1] = (uint16_t)(plane[c] >> 16);
-      dst[2] = (uint16_t)(plane[c] >> 32);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t p = plane[c][h];
+        plane[c][h] = p | (sgn[h] & (((p << 1) | (p << 2)) & 0x924924u));
+      }
+      dst[0] = (uint16_t)plane[c][0];
+      dst[1] = (uint16_t)((plane[c][0] >> 16) | (plane[c][1] << 8));
+      dst[2] = (uint16_t)(plane[c][1] >> 8);
     }
     e3 = E - base;
   }
@@ -139,39 +148,47 @@ __global__ __launch_bounds__(256) void k_quantize_packed(const float* __restrict
   }
 }
 
-// One lane per group: y = +-q * 2^(E - 127 - (m - 1)).
+// y = +-q * 2^(E - 127 - (m - 1)), a lane per four consecutive values (so that
+// a wave stores 1 KB in one piece; a lane per group took 110 us on 64M values
+// at m = 4), kPdqQuads of them per lane.
+constexpr int kPdqQuads = 4;
 template <int NP>
 __global__ __launch_bounds__(256) void k_dequantize_packed(const uint8_t* __restrict__ mant,
                                                            const uint32_t* __restrict__ expw, int64_t ngroups, int m,
                                                            float* __restrict__ y) {
-  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (gid >= ngroups) return;
+  const int64_t q0 = (int64_t)blockIdx.x * (256 * kPdqQuads) + threadIdx.x, nquads = 4 * ngroups;
   const uint32_t base = packed_base(expw[0]);
-  const int e = (int)(base + packed_exponent_offset(expw, gid)) - 127 - (m - 1);
-  uint64_t plane[NP];
+  int q[kPdqQuads][4], e[kPdqQuads];
 #pragma unroll
-  for (int c = 0; c < NP; ++c) {
-    const uint16_t* src = reinterpret_cast<const uint16_t*>(mant + (c * ngroups + gid) * 6);
-    plane[c] = (uint64_t)src[0] | ((uint64_t)src[1] << 16) | ((uint64_t)src[2] << 32);
-  }
-  float4* dst = reinterpret_cast<float4*>(y + gid * 16);
+  for (int i = 0; i < kPdqQuads; ++i) {
+    const int64_t at = min(q0 + 256 * i, nquads - 1), gid = at >> 2;  // (quads past the end reread the last one)
+    const int k = (int)(at & 3);
+    e[i] = (int)(base + packed_exponent_offset(expw, gid)) - 127 - (m - 1);
+    uint32_t f[NP], neg = 0u;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    float v[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int t = 4 * i + k;
-      int q = 0;
-      bool neg = false;
-#pragma unroll
-      for (int c = 0; c < NP; ++c) {
-        const uint32_t f = (uint32_t)(plane[c] >> (3 * t)) & 7u;
-        q = 4 * q + (int)(f & 3u);
-        neg |= (f & 4u) != 0;
-      }
-      v[k] = ldexpf((float)(neg ? -q : q), e);
+    for (int c = 0; c < NP; ++c) {
+      // fields 4k .. 4k + 3: 12 bits from bit 12 k of the group's 48
+      const uint16_t* src = reinterpret_cast<const uint16_t*>(mant + (c * ngroups + gid) * 6);
+      const int h = (3 * k) >> 2;
+      const uint32_t w = (uint32_t)src[h] | ((uint32_t)src[min(h + 1, 2)] << 16);
+      f[c] = (w >> (12 * k - 16 * h)) & 0xFFFu;
+      neg |= f[c];
     }
-    dst[i] = make_float4(v[0], v[1], v[2], v[3]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      int v = 0;
+#pragma unroll
+      for (int c = 0; c < NP; ++c) v = 4 * v + (int)((f[c] >> (3 * t)) & 3u);
+      q[i][t] = (neg >> (3 * t + 2)) & 1u ? -v : v;
+    }
+  }
+  typedef float f4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+  for (int i = 0; i < kPdqQuads; ++i) {
+    const int64_t at = q0 + 256 * i;
+    if (at < nquads)
+      stream_store(reinterpret_cast<f4*>(y) + at, f4{ldexpf((float)q[i][0], e[i]), ldexpf((float)q[i][1], e[i]),
+                                                     ldexpf((float)q[i][2], e[i]), ldexpf((float)q[i][3], e[i])});
   }
 }
 
@@ -202,8 +219,9 @@ hipError_t launch_quantize_packed(const float* x, int64_t rows, int64_t len, int
   // E_max of the tensor first (the base every group's exponent is stored above)
   hipLaunchKernelGGL(k_packed_header_clear, dim3(1), dim3(1), 0, s, expw);
   const int64_t n4 = n / 4;
-  hipLaunchKernelGGL(k_exponent_max, dim3((unsigned)((n4 + kExpMaxGranules - 1) / kExpMaxGranules)), dim3(256), 0, s,
-                     reinterpret_cast<const u32x4*>(x), n4, expw);
+  const int64_t all = (n4 + 1023) / 1024, rounds = (all + kExpMaxBlocks - 1) / kExpMaxBlocks;
+  hipLaunchKernelGGL(k_exponent_max, dim3((unsigned)((all + rounds - 1) / rounds)), dim3(256), 0, s,
+                     reinterpret_cast<const u32x4*>(x), n4, rounds, expw);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (mode == kStochastic) return quantize_packed_mode<kStochastic>(x, ngroups, m, seed, mant, expw, status, s);
@@ -214,7 +232,7 @@ hipError_t launch_quantize_packed(const float* x, int64_t rows, int64_t len, int
 hipError_t launch_dequantize_packed(const uint8_t* mant, const uint8_t* exps, int64_t rows, int64_t len, int m,
                                     float* y, hipStream_t s) {
   const int64_t ngroups = rows * len / 16;
-  const dim3 grid((unsigned)((ngroups + 255) / 256));
+  const dim3 grid((unsigned)((4 * ngroups + 256 * kPdqQuads - 1) / (256 * kPdqQuads)));
   const uint32_t* expw = reinterpret_cast<const uint32_t*>(exps);
   switch ((m + 1) / 2) {
     case 1: hipLaunchKernelGGL(k_dequantize_packed<1>, grid, dim3(256), 0, s, mant, expw, ngroups, m, y); break;

@@ -38,3 +38,30 @@ def test_dequantize_blocks(g):
             q, E, _ = oracle.quantize(x, g=g, m=m, threads=THREADS)
             out = torch.full((rows, 64), float("nan"), device="cuda")
             assert np.array_equal(fb.dequantize(t, out=out).cpu().numpy(), oracle.dequantize(q, E, g, m))
+
+
+@pytest.mark.parametrize("m", range(1, 9))
+@pytest.mark.parametrize("g", [4, 8, 16, 64])
+def test_whole_word_repacks(g, m):
+    """The repacks that move whole words of codes (packed storage at g = 16,
+    groups of 4 and 8; groups of 64 in bfp_gemm_ws) at every width: the
+    repacked tensor stands for the same values, and the product's terms are the
+    general kernel's."""
+    for rows, length in ((1, 64), (17, 192), (130, 64 * 17)):
+        announce("whole-word repack g=%d m=%d %dx%d" % (g, m, rows, length))
+        x = synth.draw("grads", (rows, length), 1000 + rows)
+        x[0, :16] = 0.0
+        xt = torch.from_numpy(x).cuda()
+        t = fb.quantize_packed(xt, m=m, rounding="stochastic", seed=5) if g == 16 else fb.quantize(xt, g=g, m=m)
+        want = (fb.dequantize_packed(t) if g == 16 else fb.dequantize(t)).cpu().numpy()
+        got = fb.dequantize(fb.repack(t)).cpu().numpy()
+        if g < 16:  # a group's values, then zeros
+            got = got.reshape(rows, length // g, 16)
+            assert not got[:, :, g:].any()
+            got = got[:, :, :g].reshape(rows, length)
+        assert np.array_equal(got.view(np.uint32) & 0x7FFFFFFF, want.view(np.uint32) & 0x7FFFFFFF)
+        assert np.array_equal(got, want)
+        f = fb.gemm_packed if g == 16 else fb.gemm
+        for use in {m, m - 2 if m in (5, 6) else m - 4 if m > 6 else m}:
+            C, D = f(t, t, use, use), f(t, t, use, use, workspace=False)
+            assert float((C - D).abs().max()) <= 2e-6 * float(D.abs().max())
