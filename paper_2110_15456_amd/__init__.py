@@ -14,6 +14,7 @@ runs in the library's HIP kernels; there is no CPU path.
 from __future__ import annotations
 
 import ctypes
+import functools
 import math
 from dataclasses import dataclass
 
@@ -41,6 +42,19 @@ def quantized_sizes(rows: int, length: int, g: int, m: int):
     return mb.value, eb.value
 
 
+# Bytes of a 16-value unit's codes in all planes, by width (the layout of
+# include/fastbfp.h).
+_UNIT_BYTES = (0, 8, 8, 12, 12, 20, 20, 24, 24)
+
+
+def _mant_bytes(rows, length, g, m):
+    """quantized_sizes' mantissa bytes without a call for the sizes it accepts."""
+    if type(m) is int and 1 <= m <= 8 and g in (4, 8, 16, 32, 64) and rows >= 0 and length >= 0 \
+            and length % (g if g > 16 else 16) == 0:
+        return rows * (length // 16) * _UNIT_BYTES[m]
+    return quantized_sizes(rows, length, g, m)[0]
+
+
 @dataclass
 class BFPTensor:
     """A rows x len BFP tensor, groups of g along len (see include/fastbfp.h).
@@ -65,13 +79,20 @@ class BFPTensor:
 
     @staticmethod
     def empty(rows: int, length: int, g: int, m: int, device) -> "BFPTensor":
-        mb, eb = quantized_sizes(rows, length, g, m)
+        mb = _mant_bytes(rows, length, g, m)
         return BFPTensor(torch.empty(mb, dtype=torch.uint8, device=device),
                          torch.empty((rows, length // g), dtype=torch.uint8, device=device), rows, length, g, m)
 
 
-def _stream(dev: torch.device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+# Pointers, streams and seeds are passed as plain integers: the library's
+# argtypes convert them, without a ctypes object per argument.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(dev: torch.device) -> int:
+    if _raw_stream is not None and dev.index is not None:
+        return _raw_stream(dev.index)
+    return torch.cuda.current_stream(dev).cuda_stream
 
 
 def _need_cuda(t: torch.Tensor, name: str, dtype=None):
@@ -101,23 +122,19 @@ def quantize(x: torch.Tensor, group_axis: int = -1, g: int = 16, m: int = 4, rou
     nd = x.dim()
     ax = group_axis % nd
     length = x.shape[ax]
-    rows = math.prod(x.shape[:ax]) * math.prod(x.shape[ax + 1:])
+    rows = x.numel() // length if length else math.prod(x.shape[:ax]) * math.prod(x.shape[ax + 1:])
     t = out if out is not None else BFPTensor.empty(rows, length, g, m, x.device)
     if (t.rows, t.len, t.g, t.m) != (rows, length, g, m):
         raise ValueError("out has the wrong shape or format")
-    st_ptr = None
-    if status is not None:
-        _need_cuda(status, "status")
-        st_ptr = ctypes.c_void_p(status.data_ptr())
-    seed_c = ctypes.c_uint64(seed & 0xFFFFFFFFFFFFFFFF)
-    ptrs = (ctypes.c_void_p(t.mant.data_ptr()), ctypes.c_void_p(t.exp.data_ptr()), st_ptr, _stream(x.device))
+    seed_c = seed & 0xFFFFFFFFFFFFFFFF
+    ptrs = (t.mant.data_ptr(), t.exp.data_ptr(), _status_ptr(status), _stream(x.device))
     if ax == nd - 1 or (nd == 2 and ax == 0):  # the 2-D entry point: rows of [R, C], or its columns
         R, C = (rows, length) if ax == nd - 1 else tuple(x.shape)
-        check(load().bfp_quantize(ctypes.c_void_p(x.data_ptr()), R, C, 1 if ax == nd - 1 else 0, g, m,
+        check(load().bfp_quantize(x.data_ptr(), R, C, 1 if ax == nd - 1 else 0, g, m,
                                   ROUNDING[rounding], seed_c, *ptrs), "bfp_quantize")
     else:
         shape = (ctypes.c_int64 * nd)(*x.shape)
-        check(load().bfp_quantize_nd(ctypes.c_void_p(x.data_ptr()), nd, shape, ax, g, m, ROUNDING[rounding], seed_c,
+        check(load().bfp_quantize_nd(x.data_ptr(), nd, shape, ax, g, m, ROUNDING[rounding], seed_c,
                                      *ptrs), "bfp_quantize_nd")
     return t
 
@@ -126,7 +143,7 @@ def _status_ptr(status):
     if status is None:
         return None
     _need_cuda(status, "status")
-    return ctypes.c_void_p(status.data_ptr())
+    return status.data_ptr()
 
 
 def _dual_outputs(R, C, g, m, device, out_rows, out_cols):
@@ -150,11 +167,9 @@ def quantize_dual(x: torch.Tensor, g: int = 16, m: int = 4, rounding: str = "nea
         raise ValueError("x must be 2-D")
     R, C = x.shape
     tr, tc = _dual_outputs(R, C, g, m, x.device, out_rows, out_cols)
-    check(load().bfp_quantize_dual(ctypes.c_void_p(x.data_ptr()), R, C, g, m, ROUNDING[rounding],
-                                   ctypes.c_uint64(seed_rows & 0xFFFFFFFFFFFFFFFF),
-                                   ctypes.c_uint64(seed_cols & 0xFFFFFFFFFFFFFFFF), ctypes.c_void_p(tr.mant.data_ptr()),
-                                   ctypes.c_void_p(tr.exp.data_ptr()), ctypes.c_void_p(tc.mant.data_ptr()),
-                                   ctypes.c_void_p(tc.exp.data_ptr()), _status_ptr(status), _stream(x.device)),
+    check(load().bfp_quantize_dual(x.data_ptr(), R, C, g, m, ROUNDING[rounding],
+                                   seed_rows & 0xFFFFFFFFFFFFFFFF, seed_cols & 0xFFFFFFFFFFFFFFFF, tr.mant.data_ptr(),
+                                   tr.exp.data_ptr(), tc.mant.data_ptr(), tc.exp.data_ptr(), _status_ptr(status), _stream(x.device)),
           "bfp_quantize_dual")
     return tr, tc
 
@@ -180,12 +195,10 @@ def weight_update(w: torch.Tensor, dw: torch.Tensor, alpha: float, g: int = 16, 
         if w_out.shape != w.shape:
             raise ValueError("w_out has the wrong shape")
     tr, tc = _dual_outputs(R, C, g, m, w.device, out_rows, out_cols)
-    check(load().bfp_weight_update(ctypes.c_void_p(w.data_ptr()), ctypes.c_void_p(dw.data_ptr()), ctypes.c_float(alpha),
-                                   ctypes.c_void_p(w_out.data_ptr()), R, C, g, m, ROUNDING[rounding],
-                                   ctypes.c_uint64(seed_rows & 0xFFFFFFFFFFFFFFFF),
-                                   ctypes.c_uint64(seed_cols & 0xFFFFFFFFFFFFFFFF), ctypes.c_void_p(tr.mant.data_ptr()),
-                                   ctypes.c_void_p(tr.exp.data_ptr()), ctypes.c_void_p(tc.mant.data_ptr()),
-                                   ctypes.c_void_p(tc.exp.data_ptr()), _status_ptr(status), _stream(w.device)),
+    check(load().bfp_weight_update(w.data_ptr(), dw.data_ptr(), alpha,
+                                   w_out.data_ptr(), R, C, g, m, ROUNDING[rounding],
+                                   seed_rows & 0xFFFFFFFFFFFFFFFF, seed_cols & 0xFFFFFFFFFFFFFFFF, tr.mant.data_ptr(),
+                                   tr.exp.data_ptr(), tc.mant.data_ptr(), tc.exp.data_ptr(), _status_ptr(status), _stream(w.device)),
           "bfp_weight_update")
     return w_out, tr, tc
 
@@ -227,11 +240,11 @@ def quantize_adaptive(x: torch.Tensor, group_axis: int = -1, g: int = 16, roundi
     st_ptr = None
     if status is not None:
         _need_cuda(status, "status")
-        st_ptr = ctypes.c_void_p(status.data_ptr())
-    check(lib.bfp_quantize_adaptive(ctypes.c_void_p(x.data_ptr()), R, C, axis_flag, g, ROUNDING[rounding],
-                                    ctypes.c_uint64(seed & 0xFFFFFFFFFFFFFFFF), ctypes.c_void_p(t4.mant.data_ptr()),
-                                    ctypes.c_void_p(t2.mant.data_ptr()) if t2 is not None else None,
-                                    ctypes.c_void_p(t4.exp.data_ptr()), ctypes.c_void_p(work.data_ptr()), st_ptr,
+        st_ptr = status.data_ptr()
+    check(lib.bfp_quantize_adaptive(x.data_ptr(), R, C, axis_flag, g, ROUNDING[rounding],
+                                    seed & 0xFFFFFFFFFFFFFFFF, t4.mant.data_ptr(),
+                                    t2.mant.data_ptr() if t2 is not None else None,
+                                    t4.exp.data_ptr(), work.data_ptr(), st_ptr,
                                     _stream(x.device)), "bfp_quantize_adaptive")
     return t4, t2, sums
 
@@ -262,11 +275,11 @@ def quantize_adaptive_noalloc(x: torch.Tensor, t4: BFPTensor, sums: torch.Tensor
         raise ValueError("t4 / t2 have the wrong shape or format")
     if sums.numel() < 2:
         raise ValueError("sums needs 2 doubles")
-    check(load().bfp_quantize_adaptive_noalloc(ctypes.c_void_p(x.data_ptr()), R, C, axis_flag, t4.g, ROUNDING[rounding],
-                                               ctypes.c_uint64(seed & 0xFFFFFFFFFFFFFFFF),
-                                               ctypes.c_void_p(t4.mant.data_ptr()),
-                                               ctypes.c_void_p(t2.mant.data_ptr()) if t2 is not None else None,
-                                               ctypes.c_void_p(t4.exp.data_ptr()), ctypes.c_void_p(sums.data_ptr()),
+    check(load().bfp_quantize_adaptive_noalloc(x.data_ptr(), R, C, axis_flag, t4.g, ROUNDING[rounding],
+                                               seed & 0xFFFFFFFFFFFFFFFF,
+                                               t4.mant.data_ptr(),
+                                               t2.mant.data_ptr() if t2 is not None else None,
+                                               t4.exp.data_ptr(), sums.data_ptr(),
                                                _status_ptr(status), _stream(x.device)), "bfp_quantize_adaptive_noalloc")
 
 
@@ -286,8 +299,8 @@ def dequantize(t: BFPTensor, out: torch.Tensor | None = None) -> torch.Tensor:
     """BFP -> FP32 [rows, len]: +-q * 2^(E - 127 - (m-1))."""
     y = out if out is not None else torch.empty((t.rows, t.len), dtype=torch.float32, device=t.device)
     _need_cuda(y, "out", torch.float32)
-    check(load().bfp_dequantize(ctypes.c_void_p(t.mant.data_ptr()), ctypes.c_void_p(t.exp.data_ptr()), t.rows,
-                                t.len, t.g, t.m, ctypes.c_void_p(y.data_ptr()), _stream(t.device)), "bfp_dequantize")
+    check(load().bfp_dequantize(t.mant.data_ptr(), t.exp.data_ptr(), t.rows,
+                                t.len, t.g, t.m, y.data_ptr(), _stream(t.device)), "bfp_dequantize")
     return y
 
 
@@ -308,8 +321,28 @@ def gemm_ws_size(A, B, m_a: int | None = None, m_b: int | None = None) -> int:
     return nb.value
 
 
+@functools.lru_cache(maxsize=4096)
+def _full_ws(a_m, b_m, M, N, K, g, m_a, m_b, packed):
+    """Workspace bytes of bfp_gemm_ws with room for a product's parts (a
+    function of the sizes and widths alone)."""
+    nb = ctypes.c_size_t(0)
+    check(load().bfp_gemm_ws_full_size(a_m, b_m, M, N, K, g, m_a, m_b, packed, ctypes.byref(nb)),
+          "bfp_gemm_ws_full_size")
+    return nb.value
+
+
+@functools.lru_cache(maxsize=4096)
+def _bfp_ws(a_m, b_m, M, N, K, g, m_a, m_b):
+    """Workspace bytes of bfp_gemm_bfp_ws."""
+    nb = ctypes.c_size_t(0)
+    check(load().bfp_gemm_bfp_ws_size(a_m, b_m, M, N, K, g, m_a, m_b, ctypes.byref(nb)), "bfp_gemm_bfp")
+    return nb.value
+
+
 def _gemm_out(A, B, out):
-    C = out if out is not None else torch.empty((A.rows, B.rows), dtype=torch.float32, device=A.device)
+    if out is None:
+        return torch.empty((A.rows, B.rows), dtype=torch.float32, device=A.device)
+    C = out
     _need_cuda(C, "out", torch.float32)
     if C.dim() != 2 or C.shape[0] != A.rows or C.shape[1] != B.rows:
         raise ValueError("out must be [%d, %d]" % (A.rows, B.rows))
@@ -330,14 +363,11 @@ def _gemm_with_workspace(A, B, m_a, m_b, C, workspace):
         elif not workspace.is_cuda or workspace.dtype != torch.uint8 or not workspace.is_contiguous():
             ws = None  # none is needed
     else:
-        nb = ctypes.c_size_t(0)
-        check(load().bfp_gemm_ws_full_size(A.m, B.m, A.rows, B.rows, A.len, A.g, m_a, m_b, packed, ctypes.byref(nb)),
-              "bfp_gemm_ws_full_size")
-        ws = torch.empty(nb.value, dtype=torch.uint8, device=A.device) if nb.value else None
-    check(load().bfp_gemm_ws(ctypes.c_void_p(A.mant.data_ptr()), ctypes.c_void_p(A.exp.data_ptr()), A.m,
-                             ctypes.c_void_p(B.mant.data_ptr()), ctypes.c_void_p(B.exp.data_ptr()), B.m, A.rows,
-                             B.rows, A.len, A.g, m_a, m_b, packed, ctypes.c_void_p(C.data_ptr()), C.stride(0),
-                             ctypes.c_void_p(ws.data_ptr()) if ws is not None else None,
+        need = _full_ws(A.m, B.m, A.rows, B.rows, A.len, A.g, m_a, m_b, packed)
+        ws = torch.empty(need, dtype=torch.uint8, device=A.device) if need else None
+    check(load().bfp_gemm_ws(A.mant.data_ptr(), A.exp.data_ptr(), A.m, B.mant.data_ptr(), B.exp.data_ptr(), B.m, A.rows,
+                             B.rows, A.len, A.g, m_a, m_b, packed, C.data_ptr(), C.stride(0),
+                             ws.data_ptr() if ws is not None else None,
                              ws.numel() if ws is not None else 0, _stream(A.device)), "bfp_gemm_ws")
     return C
 
@@ -361,9 +391,9 @@ def gemm(A: BFPTensor, B: BFPTensor, m_a: int | None = None, m_b: int | None = N
     C = _gemm_out(A, B, out)
     if tile is None and workspace is not False:
         return _gemm_with_workspace(A, B, m_a, m_b, C, workspace)
-    args = (ctypes.c_void_p(A.mant.data_ptr()), ctypes.c_void_p(A.exp.data_ptr()), A.m,
-            ctypes.c_void_p(B.mant.data_ptr()), ctypes.c_void_p(B.exp.data_ptr()), B.m, A.rows, B.rows,
-            A.len, A.g, m_a, m_b, ctypes.c_void_p(C.data_ptr()), C.stride(0))
+    args = (A.mant.data_ptr(), A.exp.data_ptr(), A.m,
+            B.mant.data_ptr(), B.exp.data_ptr(), B.m, A.rows, B.rows,
+            A.len, A.g, m_a, m_b, C.data_ptr(), C.stride(0))
     if tile is None:
         check(load().bfp_gemm(*args, _stream(A.device)), "bfp_gemm")
     else:
@@ -382,9 +412,9 @@ def repack(t, m_use: int | None = None) -> BFPTensor:
     r = BFPTensor(torch.empty(mb.value, dtype=torch.uint8, device=t.device),
                   torch.empty((t.rows, lo.value // go.value), dtype=torch.uint8, device=t.device), t.rows, lo.value,
                   go.value, m_use)
-    check(load().bfp_repack(ctypes.c_void_p(t.mant.data_ptr()), ctypes.c_void_p(t.exp.data_ptr()), t.rows, t.len, t.g,
-                            t.m, 1 if isinstance(t, PackedBFPTensor) else 0, m_use, ctypes.c_void_p(r.mant.data_ptr()),
-                            ctypes.c_void_p(r.exp.data_ptr()), _stream(t.device)), "bfp_repack")
+    check(load().bfp_repack(t.mant.data_ptr(), t.exp.data_ptr(), t.rows, t.len, t.g,
+                            t.m, 1 if isinstance(t, PackedBFPTensor) else 0, m_use, r.mant.data_ptr(),
+                            r.exp.data_ptr(), _stream(t.device)), "bfp_repack")
     return r
 
 
@@ -403,16 +433,15 @@ def gemm_bfp(A: BFPTensor, B: BFPTensor, c_m: int, m_a: int | None = None, m_b: 
     st_ptr = None
     if status is not None:
         _need_cuda(status, "status")
-        st_ptr = ctypes.c_void_p(status.data_ptr())
-    nb = ctypes.c_size_t(0)
-    check(load().bfp_gemm_bfp_ws_size(A.m, B.m, A.rows, B.rows, A.len, A.g, m_a, m_b, ctypes.byref(nb)), "bfp_gemm_bfp")
-    ws = torch.empty(nb.value, dtype=torch.uint8, device=A.device) if nb.value else None
-    check(load().bfp_gemm_bfp_ws(ctypes.c_void_p(A.mant.data_ptr()), ctypes.c_void_p(A.exp.data_ptr()), A.m,
-                                 ctypes.c_void_p(B.mant.data_ptr()), ctypes.c_void_p(B.exp.data_ptr()), B.m, A.rows,
+        st_ptr = status.data_ptr()
+    need = _bfp_ws(A.m, B.m, A.rows, B.rows, A.len, A.g, m_a, m_b)
+    ws = torch.empty(need, dtype=torch.uint8, device=A.device) if need else None
+    check(load().bfp_gemm_bfp_ws(A.mant.data_ptr(), A.exp.data_ptr(), A.m,
+                                 B.mant.data_ptr(), B.exp.data_ptr(), B.m, A.rows,
                                  B.rows, A.len, A.g, m_a, m_b, c_m, ROUNDING[rounding],
-                                 ctypes.c_uint64(seed & 0xFFFFFFFFFFFFFFFF), ctypes.c_void_p(t.mant.data_ptr()),
-                                 ctypes.c_void_p(t.exp.data_ptr()), st_ptr,
-                                 ctypes.c_void_p(ws.data_ptr()) if ws is not None else None, nb.value,
+                                 seed & 0xFFFFFFFFFFFFFFFF, t.mant.data_ptr(),
+                                 t.exp.data_ptr(), st_ptr,
+                                 ws.data_ptr() if ws is not None else None, need,
                                  _stream(A.device)), "bfp_gemm_bfp")
     return t
 
@@ -421,8 +450,8 @@ def gemm_group_partials(A: BFPTensor, B: BFPTensor, m_a: int | None = None, m_b:
     """Exact int32 group partials P [K/g, M, N] (int8 MFMA)."""
     m_a, m_b = _gemm_args(A, B, m_a, m_b)
     P = torch.empty((A.len // A.g, A.rows, B.rows), dtype=torch.int32, device=A.device)
-    check(load().bfp_gemm_group_partials(ctypes.c_void_p(A.mant.data_ptr()), A.m, ctypes.c_void_p(B.mant.data_ptr()),
-                                         B.m, A.rows, B.rows, A.len, A.g, m_a, m_b, ctypes.c_void_p(P.data_ptr()),
+    check(load().bfp_gemm_group_partials(A.mant.data_ptr(), A.m, B.mant.data_ptr(),
+                                         B.m, A.rows, B.rows, A.len, A.g, m_a, m_b, P.data_ptr(),
                                          _stream(A.device)), "bfp_gemm_group_partials")
     return P
 
@@ -471,9 +500,9 @@ def quantize_packed(x: torch.Tensor, m: int = 4, rounding: str = "nearest", seed
     C = x.shape[-1]
     R = math.prod(x.shape[:-1])
     t = PackedBFPTensor.empty(R, C, m, x.device)
-    check(load().bfp_quantize_packed(ctypes.c_void_p(x.data_ptr()), R, C, m, ROUNDING[rounding],
-                                     ctypes.c_uint64(seed & 0xFFFFFFFFFFFFFFFF), ctypes.c_void_p(t.mant.data_ptr()),
-                                     ctypes.c_void_p(t.exp.data_ptr()), _status_ptr(status), _stream(x.device)),
+    check(load().bfp_quantize_packed(x.data_ptr(), R, C, m, ROUNDING[rounding],
+                                     seed & 0xFFFFFFFFFFFFFFFF, t.mant.data_ptr(),
+                                     t.exp.data_ptr(), _status_ptr(status), _stream(x.device)),
           "bfp_quantize_packed")
     return t
 
@@ -482,8 +511,8 @@ def dequantize_packed(t: PackedBFPTensor, out: torch.Tensor | None = None) -> to
     """Packed BFP -> FP32 [rows, len]."""
     y = out if out is not None else torch.empty((t.rows, t.len), dtype=torch.float32, device=t.device)
     _need_cuda(y, "out", torch.float32)
-    check(load().bfp_dequantize_packed(ctypes.c_void_p(t.mant.data_ptr()), ctypes.c_void_p(t.exp.data_ptr()), t.rows,
-                                       t.len, t.m, ctypes.c_void_p(y.data_ptr()), _stream(t.device)),
+    check(load().bfp_dequantize_packed(t.mant.data_ptr(), t.exp.data_ptr(), t.rows,
+                                       t.len, t.m, y.data_ptr(), _stream(t.device)),
           "bfp_dequantize_packed")
     return y
 
@@ -497,8 +526,8 @@ def gemm_packed(A: PackedBFPTensor, B: PackedBFPTensor, m_a: int | None = None, 
     C = _gemm_out(A, B, out)
     if workspace is not False:
         return _gemm_with_workspace(A, B, m_a, m_b, C, workspace)
-    check(load().bfp_gemm_packed(ctypes.c_void_p(A.mant.data_ptr()), ctypes.c_void_p(A.exp.data_ptr()), A.m,
-                                 ctypes.c_void_p(B.mant.data_ptr()), ctypes.c_void_p(B.exp.data_ptr()), B.m, A.rows,
-                                 B.rows, A.len, m_a, m_b, ctypes.c_void_p(C.data_ptr()), C.stride(0),
+    check(load().bfp_gemm_packed(A.mant.data_ptr(), A.exp.data_ptr(), A.m,
+                                 B.mant.data_ptr(), B.exp.data_ptr(), B.m, A.rows,
+                                 B.rows, A.len, m_a, m_b, C.data_ptr(), C.stride(0),
                                  _stream(A.device)), "bfp_gemm_packed")
     return C

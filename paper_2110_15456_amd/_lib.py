@@ -71,6 +71,8 @@ class BFPError(RuntimeError):
 def load() -> ctypes.CDLL:
     """Load libfastbfp.so once; raise if it is absent or incompatible."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(LIB_PATH):
