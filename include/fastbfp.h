@@ -330,10 +330,10 @@ int bfp_gemm_bfp(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, cons
  * bfp_gemm_bfp_ws -- bfp_gemm_bfp with a caller workspace (section V-A): exactly
  * bfp_quantize(C, group axis 1, g = 16, ...) of the FP32 C that bfp_gemm_ws
  * computes with a workspace of bfp_gemm_ws_full_size bytes.  Products that
- * bfp_gemm_ws takes in parts or on the few-output kernel leave their FP32 sums
- * in the workspace (bfp_gemm_bfp_ws_size bytes, 256-byte aligned), from which a
- * second kernel converts them; the others need none (size 0, NULL).  With a
- * smaller workspace it is bfp_gemm_bfp.
+ * bfp_gemm_ws takes in parts leave their FP32 sums in the workspace
+ * (bfp_gemm_bfp_ws_size bytes, 256-byte aligned), from which a second kernel
+ * converts them; the others need none (size 0, NULL).  With a smaller workspace
+ * such a product is summed in one run over K, as bfp_gemm_ws does it then.
  */
 int bfp_gemm_bfp_ws_size(int a_m_bits, int b_m_bits, int64_t M, int64_t N, int64_t K, int g, int m_a, int m_b,
                          size_t* bytes);

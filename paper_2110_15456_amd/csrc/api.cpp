@@ -304,7 +304,7 @@ int bfp_gemm_bfp_ws_size(int a_m_bits, int b_m_bits, int64_t M, int64_t N, int64
   if (M == 0 || N == 0) return BFP_OK;
   const fastbfp::GemmPlan plan =
       fastbfp::gemm_plan(a_m_bits, planes_used(a_m_bits, m_a), b_m_bits, planes_used(b_m_bits, m_b), M, N, K, g);
-  if (plan.parts > 1 || plan.rm > 0) *bytes = parts_bytes(plan.parts, M, N);
+  if (plan.parts > 1) *bytes = parts_bytes(plan.parts, M, N);
   return BFP_OK;
 }
 
@@ -318,7 +318,11 @@ int bfp_gemm_bfp_ws(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, c
   const int na = planes_used(a_m_bits, m_a), nb = planes_used(b_m_bits, m_b);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const fastbfp::GemmPlan plan = fastbfp::gemm_plan(a_m_bits, na, b_m_bits, nb, M, N, K, g);
-  if ((plan.parts == 1 && plan.rm == 0) || !workspace || !aligned(workspace, 256) ||
+  if (plan.rm > 0)
+    return status_of(fastbfp::launch_gemm_direct_bfp(plan, a_mant, a_exp, a_m_bits, na, b_mant, b_exp, b_m_bits, nb, M,
+                                                     N, K, g, 4 - m_a - m_b, c_m_bits, round_mode, seed, c_mant, c_exp,
+                                                     status_word, s));
+  if (plan.parts == 1 || !workspace || !aligned(workspace, 256) ||
       workspace_bytes < parts_bytes(plan.parts, M, N))
     return status_of(fastbfp::launch_gemm_mx_bfp(a_mant, a_exp, a_m_bits, na, b_mant, b_exp, b_m_bits, nb, M, N, K, g,
                                                  4 - m_a - m_b, c_m_bits, round_mode, seed, c_mant, c_exp, status_word,

@@ -20,8 +20,7 @@
 // 2^-254 adds nothing); rows past the end read zeros (the buffer resource ends
 // at the last row).
 #pragma once
-#include "bfp_device.h"
-#include "launch.h"
+#include "bfp_quant.h"
 
 namespace fastbfp {
 
@@ -121,6 +120,59 @@ __device__ __forceinline__ void mma(v4f& acc, const v8i& a, const v8i& b, uint32
                                                          (int)ea);
 }
 
+// BFP output (m and mode at run time: a group per thread, once per workgroup).
+struct Out {
+  uint8_t *mant0, *mant1, *exps;
+  uint32_t* status;
+  int m, mode;
+  uint32_t key0, key1;
+};
+// Converts the 16 values at b as quantize_groups does and stores them as group
+// gid; true if one was Inf or NaN.
+__device__ __forceinline__ bool convert(const uint32_t (&b)[16], int64_t gid, const Out& o) {
+  const uint32_t E = group_exponent<16>(b), m = (uint32_t)o.m, qmax = (1u << m) - 1u;
+  uint32_t q[16], noise[4] = {0u, 0u, 0u, 0u};
+  if (o.mode == kStochastic) {
+    group_noise<16>((uint64_t)gid, o.key0, o.key1, noise);
+#pragma unroll
+    for (int t = 0; t < 16; ++t)
+      q[t] = value_magnitude<kStochastic, false>(b[t], magnitude_align<kStochastic>(m, E), noise[t >> 2], t, qmax);
+  } else if (o.mode == kNearest) {
+#pragma unroll
+    for (int t = 0; t < 16; ++t)
+      q[t] = value_magnitude<kNearest, false>(b[t], magnitude_align<kNearest>(m, E), 0u, t, qmax);
+  } else {
+#pragma unroll
+    for (int t = 0; t < 16; ++t)
+      q[t] = value_magnitude<kTruncate, false>(b[t], magnitude_align<kTruncate>(m, E), 0u, t, qmax);
+  }
+  const uint32_t lo_bits = m <= 4 ? 0u : (uint32_t)low_chunk_bits(o.m), lo_mask = (1u << lo_bits) - 1u;
+  uint32_t w0[4] = {0u, 0u, 0u, 0u}, w1[4] = {0u, 0u, 0u, 0u};
+  auto put6 = [](uint32_t(&w)[4], int t, uint32_t code) {
+    const int wi = 6 * t >> 5, sh = 6 * t & 31;
+    w[wi] |= code << sh;
+    if (sh > 26) w[wi + 1] |= code >> (32 - sh);
+  };
+#pragma unroll
+  for (int t = 0; t < 16; ++t) {
+    const uint32_t neg = b[t] >> 31, hi = q[t] >> lo_bits, lo = q[t] & lo_mask;
+    if (m <= 2) w0[t >> 3] |= (hi ? (neg << 3) | hi : 0u) << (4 * (t & 7));
+    else put6(w0, t, hi ? (neg << 5) | e2m3_half_code(hi) : 0u);
+    if (m > 4) put6(w1, t, lo ? (neg << 5) | (m > 6 ? e2m3_half_code(lo) : lo) : 0u);
+  }
+  o.exps[gid] = (uint8_t)E;
+  if (m <= 2) store_plane<16, true>(o.mant0, gid, w0);
+  else store_plane<16, false>(o.mant0, gid, w0);
+  if (m > 6) {
+    store_plane<16, false>(o.mant1, gid, w1);
+  } else if (m > 4) {
+    const uint2 d = lo2_pack(w1[0], w1[1], w1[2]);
+    const uint32_t w[2] = {d.x, d.y};
+    store_plane<16, true>(o.mant1, gid, w);
+  }
+  return E == 255u;
+}
+
 // One row tile's fragments of one superstep.
 template <int NP, int K0, int K1> struct Frag {
   Units<K0> p0;
@@ -131,11 +183,12 @@ template <int NP, int K0, int K1> struct Frag {
 }  // namespace direct
 
 // NA / NB, FA / FB, G: as mx::Cfg (planes read; FP4 codes, or split at 2 bits).
-template <int NA, int NB, int FA, int FB, int G, int RM, int RN>
+// BOUT: C is written as BFP (N a multiple of 16).
+template <int NA, int NB, int FA, int FB, int G, int RM, int RN, bool BOUT>
 __global__ __launch_bounds__(64 * direct::kMaxWaves) void k_gemm_direct(
     const uint8_t* __restrict__ a_mant, const uint8_t* __restrict__ a_exp, int64_t a_ps,
     const uint8_t* __restrict__ b_mant, const uint8_t* __restrict__ b_exp, int64_t b_ps, int M, int N, int ng,
-    float scale, float* __restrict__ C, int64_t ldc) {
+    float scale, float* __restrict__ C, int64_t ldc, direct::Out out) {
   using namespace direct;
   constexpr int KA0 = (NA == 1 && FA) ? kPlaneFP4 : kPlaneFP6, KB0 = (NB == 1 && FB) ? kPlaneFP4 : kPlaneFP6;
   constexpr int KA1 = FA ? kPlaneLo2 : kPlaneFP6, KB1 = FB ? kPlaneLo2 : kPlaneFP6;
@@ -241,7 +294,27 @@ __global__ __launch_bounds__(64 * direct::kMaxWaves) void k_gemm_direct(
     for (int j = 0; j < RN; ++j)
       *reinterpret_cast<v4f*>(&part[wave][(16 * i + lr) * SROW + 16 * j + 4 * lb]) = acc[i][j];
   __syncthreads();
-  // C: the waves' sums added in wave order, four columns per thread.
+  // C: the waves' sums added in wave order, four columns (or a group of 16) per
+  // thread.
+  if constexpr (BOUT) {
+    const int nact = min(nw, (nss + per - 1) / max(per, 1));
+    bool bad = false;
+    for (int q = threadIdx.x; q < 16 * RM * RN; q += blockDim.x) {
+      const int r = q / RN, j = q % RN;
+      uint32_t b[16];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        v4f v = *reinterpret_cast<const v4f*>(&part[0][r * SROW + 16 * j + 4 * k]);
+        for (int w = 1; w < nact; ++w) v += *reinterpret_cast<const v4f*>(&part[w][r * SROW + 16 * j + 4 * k]);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) b[4 * k + t] = __float_as_uint(v[t] * scale);
+      }
+      if (row0 + r < M && col0 + 16 * j < N)
+        bad |= convert(b, (int64_t)(row0 + r) * (N / 16) + col0 / 16 + j, out);
+    }
+    if (out.status && bad) atomicOr(out.status, 1u);
+    return;
+  }
   const bool vec = (ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0;
   const int nact = min(nw, (nss + per - 1) / max(per, 1));  // waves that had a superstep
   for (int q = threadIdx.x; q < 16 * RM * 4 * RN; q += blockDim.x) {
@@ -264,15 +337,19 @@ __global__ __launch_bounds__(64 * direct::kMaxWaves) void k_gemm_direct(
 template <int NA, int NB, int FA, int FB, int G>
 hipError_t launch_direct_t(int rm, int rn, const uint8_t* a_mant, const uint8_t* a_exp, int64_t a_ps,
                            const uint8_t* b_mant, const uint8_t* b_exp, int64_t b_ps, int M, int N, int ng, float scale,
-                           float* C, int64_t ldc, hipStream_t s) {
+                           float* C, int64_t ldc, const direct::Out* out, hipStream_t s) {
   const int nss = (ng + 15) / 16;
   const int nw = nss < 1 ? 1 : nss > direct::kMaxWaves ? direct::kMaxWaves : nss;
   const dim3 grid((unsigned)((N + 16 * rn - 1) / (16 * rn)), (unsigned)((M + 16 * rm - 1) / (16 * rm)));
-#define FASTBFP_DIRECT_LAUNCH(RM, RN)                                                                              \
-  if (rm == RM && rn == RN) {                                                                                      \
-    hipLaunchKernelGGL((k_gemm_direct<NA, NB, FA, FB, G, RM, RN>), grid, dim3(64 * nw), 0, s, a_mant, a_exp, a_ps, \
-                       b_mant, b_exp, b_ps, M, N, ng, scale, C, ldc);                                              \
-    return hipGetLastError();                                                                                      \
+#define FASTBFP_DIRECT_LAUNCH(RM, RN)                                                                                 \
+  if (rm == RM && rn == RN) {                                                                                         \
+    if (out)                                                                                                          \
+      hipLaunchKernelGGL((k_gemm_direct<NA, NB, FA, FB, G, RM, RN, true>), grid, dim3(64 * nw), 0, s, a_mant, a_exp,  \
+                         a_ps, b_mant, b_exp, b_ps, M, N, ng, scale, C, ldc, *out);                                   \
+    else                                                                                                              \
+      hipLaunchKernelGGL((k_gemm_direct<NA, NB, FA, FB, G, RM, RN, false>), grid, dim3(64 * nw), 0, s, a_mant, a_exp, \
+                         a_ps, b_mant, b_exp, b_ps, M, N, ng, scale, C, ldc, direct::Out{});                          \
+    return hipGetLastError();                                                                                         \
   }
   FASTBFP_DIRECT_LAUNCH(1, 1)
   FASTBFP_DIRECT_LAUNCH(2, 2)
@@ -285,7 +362,7 @@ hipError_t launch_direct_t(int rm, int rn, const uint8_t* a_mant, const uint8_t*
 #define FASTBFP_DIRECT_INSTANTIATE(NA, NB, FA, FB, G)                                                            \
   template hipError_t launch_direct_t<NA, NB, FA, FB, G>(int, int, const uint8_t*, const uint8_t*, int64_t,      \
                                                          const uint8_t*, const uint8_t*, int64_t, int, int, int, \
-                                                         float, float*, int64_t, hipStream_t);
+                                                         float, float*, int64_t, const direct::Out*, hipStream_t);
 #define FASTBFP_DIRECT_DECLARE(NA, NB, FA, FB, G) extern FASTBFP_DIRECT_INSTANTIATE(NA, NB, FA, FB, G)
 #define FASTBFP_DIRECT_ALL(DO, NA, NB, G) DO(NA, NB, 0, 0, G) DO(NA, NB, 0, 1, G) DO(NA, NB, 1, 0, G) DO(NA, NB, 1, 1, G)
 

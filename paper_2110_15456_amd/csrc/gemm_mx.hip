@@ -146,10 +146,11 @@ hipError_t launch_tiled(const Product& p, const Output& o, int tile) {
 }
 
 template <int NA, int NB, int G>
-hipError_t launch_direct_fmt(const Product& p, const GemmPlan& plan, float* C, int64_t ldc, hipStream_t s) {
+hipError_t launch_direct_fmt(const Product& p, const GemmPlan& plan, float* C, int64_t ldc, const direct::Out* out,
+                             hipStream_t s) {
 #define FASTBFP_DIRECT(FA, FB)                                                                                    \
   return launch_direct_t<NA, NB, FA, FB, G>(plan.rm, plan.rn, p.a_mant, p.a_exp, p.a_ps, p.b_mant, p.b_exp, p.b_ps, \
-                                            p.M, p.N, p.ng, p.scale, C, ldc, s)
+                                            p.M, p.N, p.ng, p.scale, C, ldc, out, s)
   if (!p.fa && !p.fb) FASTBFP_DIRECT(0, 0);
   if (!p.fa) FASTBFP_DIRECT(0, 1);
   if (!p.fb) FASTBFP_DIRECT(1, 0);
@@ -158,11 +159,12 @@ hipError_t launch_direct_fmt(const Product& p, const GemmPlan& plan, float* C, i
 }
 
 template <int G>
-hipError_t launch_direct(const Product& p, const GemmPlan& plan, float* C, int64_t ldc, hipStream_t s) {
-  if (p.na == 1 && p.nb == 1) return launch_direct_fmt<1, 1, G>(p, plan, C, ldc, s);
-  if (p.na == 1 && p.nb == 2) return launch_direct_fmt<1, 2, G>(p, plan, C, ldc, s);
-  if (p.na == 2 && p.nb == 1) return launch_direct_fmt<2, 1, G>(p, plan, C, ldc, s);
-  return launch_direct_fmt<2, 2, G>(p, plan, C, ldc, s);
+hipError_t launch_direct(const Product& p, const GemmPlan& plan, float* C, int64_t ldc, const direct::Out* out,
+                         hipStream_t s) {
+  if (p.na == 1 && p.nb == 1) return launch_direct_fmt<1, 1, G>(p, plan, C, ldc, out, s);
+  if (p.na == 1 && p.nb == 2) return launch_direct_fmt<1, 2, G>(p, plan, C, ldc, out, s);
+  if (p.na == 2 && p.nb == 1) return launch_direct_fmt<2, 1, G>(p, plan, C, ldc, out, s);
+  return launch_direct_fmt<2, 2, G>(p, plan, C, ldc, out, s);
 }
 
 int fmt_flag(int m, int planes) { return planes == 1 ? plane0_fp4(m) : m <= 6; }
@@ -309,9 +311,20 @@ hipError_t launch_gemm_plan(const GemmPlan& plan, const uint8_t* a_mant, const u
                             int64_t K, int g, int scale_log2, float* C, int64_t ldc, hipStream_t s) {
   if (M == 0 || N == 0) return hipSuccess;
   const Product p = make_product(a_mant, a_exp, a_m, na, b_mant, b_exp, b_m, nb, M, N, K, g, scale_log2);
-  if (plan.rm > 0) return g == 32 ? launch_direct<32>(p, plan, C, ldc, s) : launch_direct<16>(p, plan, C, ldc, s);
+  if (plan.rm > 0)
+    return g == 32 ? launch_direct<32>(p, plan, C, ldc, nullptr, s) : launch_direct<16>(p, plan, C, ldc, nullptr, s);
   const Output o{C, ldc, nullptr, plan.parts > 1 ? plan.part_slabs : 0, s};
   return g == 32 ? launch_tiled<32>(p, o, 0) : launch_tiled<16>(p, o, plan.tile);
+}
+
+hipError_t launch_gemm_direct_bfp(const GemmPlan& plan, const uint8_t* a_mant, const uint8_t* a_exp, int a_m, int na,
+                                  const uint8_t* b_mant, const uint8_t* b_exp, int b_m, int nb, int64_t M, int64_t N,
+                                  int64_t K, int g, int scale_log2, int c_m, int mode, uint64_t seed, uint8_t* c_mant,
+                                  uint8_t* c_exp, uint32_t* status, hipStream_t s) {
+  const Product p = make_product(a_mant, a_exp, a_m, na, b_mant, b_exp, b_m, nb, M, N, K, g, scale_log2);
+  const direct::Out out{c_mant, c_mant + M * (N / 16) * plane_group_bytes(16, c_m, 0), c_exp, status, c_m, mode,
+                        (uint32_t)seed, (uint32_t)(seed >> 32)};
+  return g == 32 ? launch_direct<32>(p, plan, nullptr, N, &out, s) : launch_direct<16>(p, plan, nullptr, N, &out, s);
 }
 
 }  // namespace fastbfp

@@ -121,6 +121,12 @@ int64_t gemm_plan_ld(int64_t N);
 hipError_t launch_gemm_plan(const GemmPlan& plan, const uint8_t* a_mant, const uint8_t* a_exp, int a_m, int na,
                             const uint8_t* b_mant, const uint8_t* b_exp, int b_m, int nb, int64_t M, int64_t N,
                             int64_t K, int g, int scale_log2, float* C, int64_t ldc, hipStream_t s);
+// A product planned on the few-output kernel (plan.rm > 0) with its output
+// converted there, as launch_gemm_mx_bfp converts C.
+hipError_t launch_gemm_direct_bfp(const GemmPlan& plan, const uint8_t* a_mant, const uint8_t* a_exp, int a_m, int na,
+                                  const uint8_t* b_mant, const uint8_t* b_exp, int b_m, int nb, int64_t M, int64_t N,
+                                  int64_t K, int g, int scale_log2, int c_m, int mode, uint64_t seed, uint8_t* c_mant,
+                                  uint8_t* c_exp, uint32_t* status, hipStream_t s);
 // C = the sum of the `parts` M x N matrices at p (rows gemm_plan_ld(N) apart),
 // in a fixed order; or that sum converted as launch_gemm_mx_bfp converts C.
 hipError_t launch_parts_sum(const float* p, int parts, int64_t M, int64_t N, float* C, int64_t ldc, hipStream_t s);
