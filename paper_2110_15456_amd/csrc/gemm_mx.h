@@ -117,6 +117,9 @@ struct Cfg {
   static constexpr int EXP_ROWS_PER_T = (BM + BN + NT - 1) / NT;
   // Explicitly software-pipelined fragment reads (one chunk per operand);
   // otherwise the compiler schedules them.
+  // Waves per SIMD the registers have to leave room for: two where a tile's
+  // accumulators take at most half of them (two workgroups per CU).
+  static constexpr int WAVES = TM * TN * 4 <= 128 && NA == 1 && NB == 1 ? 2 : 1;
   static constexpr bool PIPE = FASTBFP_MX_PIPE11 && NA == 1 && NB == 1 && G == 16;
   static_assert(TM * 16 * WGM == BM && TN * 16 * WGN == BN, "wave tiles cover the tile");
   static_assert((BM + BN) % 64 == 0 && BM % 64 == 0 && BN % 64 == 0,
@@ -354,6 +357,7 @@ template <int FP4> struct mfma_fmt { static constexpr int value = FP4 ? 4 : 2; }
 #define FASTBFP_MX_TIED 1
 #endif
 typedef int v6i __attribute__((ext_vector_type(6)));
+typedef int v2i __attribute__((ext_vector_type(2)));
 // acc += the block-scaled product of one K-step (A format FA, B format FB,
 // block scales sa / sb).  The intrinsic's instruction form does not tie the
 // result to the accumulator input, so with 256 accumulator registers live the
@@ -411,6 +415,38 @@ __device__ __forceinline__ void mma(v4f& acc, const v8i& a, const v8i& b, int sa
                                                          SA, sa);
 #endif
 }
+// The same on operands held in the registers the instruction reads (six for
+// FP6, four for FP4).
+template <int F> struct opnd { typedef v6i type; };
+template <> struct opnd<1> { typedef v4i type; };
+#define FASTBFP_MFMA_ASM2(SEL, CB, BG) \
+  "v_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 " SEL " cbsz:" #CB " blgp:" #BG
+#define FASTBFP_MFMA_SEL2(CB, BG)                                                                                    \
+  {                                                                                                                  \
+    if constexpr (NOP && KS == 0)                                                                                    \
+      asm(FASTBFP_MFMA_ASM("op_sel_hi:[0,0,0]", CB, BG) : "+a"(acc) : "v"(b), "v"(a), "v"(sb), "v"(sa));             \
+    else if constexpr (NOP)                                                                                          \
+      asm(FASTBFP_MFMA_ASM("op_sel:[1,1,0] op_sel_hi:[0,0,0]", CB, BG) : "+a"(acc) : "v"(b), "v"(a), "v"(sb), "v"(sa)); \
+    else if constexpr (KS == 0)                                                                                      \
+      asm(FASTBFP_MFMA_ASM2("op_sel_hi:[0,0,0]", CB, BG) : "+a"(acc) : "v"(b), "v"(a), "v"(sb), "v"(sa));            \
+    else                                                                                                             \
+      asm(FASTBFP_MFMA_ASM2("op_sel:[1,1,0] op_sel_hi:[0,0,0]", CB, BG) : "+a"(acc) : "v"(b), "v"(a), "v"(sb), "v"(sa)); \
+  }
+template <int FA, int FB, int KS, bool NOP, class A, class B>
+__device__ __forceinline__ void mma_held(v4f& acc, const A& a, const B& b, int sa, int sb) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (FA && FB)
+    FASTBFP_MFMA_SEL2(4, 4)
+  else if constexpr (FA)
+    FASTBFP_MFMA_SEL2(2, 4)
+  else if constexpr (FB)
+    FASTBFP_MFMA_SEL2(4, 2)
+  else
+    FASTBFP_MFMA_SEL2(2, 2)
+#endif
+}
+#undef FASTBFP_MFMA_SEL2
+#undef FASTBFP_MFMA_ASM2
 #undef FASTBFP_MFMA_SEL
 #undef FASTBFP_MFMA_ASM
 // Wait states between the last MFMA and any other read of its accumulators
@@ -444,7 +480,7 @@ struct OutBFP {
 };
 
 template <class CF, bool EXP_FULL, int QNCH>
-__global__ __launch_bounds__(CF::NT) void k_gemm_mx(const uint8_t* __restrict__ a_mant, const uint8_t* __restrict__ a_exp,
+__global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __restrict__ a_mant, const uint8_t* __restrict__ a_exp,
                                                  int64_t a_plane_stride, const uint8_t* __restrict__ b_mant,
                                                  const uint8_t* __restrict__ b_exp, int64_t b_plane_stride, int M,
                                                  int N, int ng, float scale, float* __restrict__ C, int64_t ldc,
@@ -492,14 +528,6 @@ __global__ __launch_bounds__(CF::NT) void k_gemm_mx(const uint8_t* __restrict__ 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;  // wave index in an SGPR
   const int wr = wave / CF::WGN, wc = wave % CF::WGN;
   const int lr = lane & 15, lb = lane >> 4;
-
-  // Zero both stages once: the slot dwords that the 12-byte loads never write
-  // are the zero padding of the FP6 operands.
-  for (int i = tid; i < SB / 16; i += NTHR) {
-    reinterpret_cast<u32x4*>(stage0)[i] = u32x4{0u, 0u, 0u, 0u};
-    reinterpret_cast<u32x4*>(stage1)[i] = u32x4{0u, 0u, 0u, 0u};
-  }
-  __syncthreads();
 
   v4f acc[TM][TN];
 #pragma unroll
@@ -649,9 +677,223 @@ __global__ __launch_bounds__(CF::NT) void k_gemm_mx(const uint8_t* __restrict__ 
   uint2 e_regs[CF::EXP_ROWS_PER_T];
   if (nslabs > 0) {
     issue(stage0, 0, true, e_regs, XP ? xe0 : nullptr);
+    // Under the first loads' latency, zero the slot dwords that 12-byte loads
+    // never write, the padding of the FP6 operands, in both stages.
+    auto zero_pads = [&](int off, int rows) {
+      for (int i = tid; i < rows * 8; i += NTHR) {
+        *reinterpret_cast<uint32_t*>(stage0 + off + 16 * i + 12) = 0u;
+        *reinterpret_cast<uint32_t*>(stage1 + off + 16 * i + 12) = 0u;
+      }
+    };
+#pragma unroll
+    for (int p = 0; p < NA; ++p)
+      if (!mx::a_four<CF>(p)) zero_pads(mx::a_plane<CF>(p), CF::BM);
+#pragma unroll
+    for (int p = 0; p < NB; ++p)
+      if (!mx::b_four<CF>(p)) zero_pads(mx::b_plane<CF>(p), CF::BN);
     put_exps(stage0, e_regs);
   }
 
+  if constexpr (CF::PIPE) {
+    // One chunk plane per operand, groups of 16: a software pipeline that runs
+    // through the slab barriers.  A block is the TN MFMAs of one A fragment (row
+    // tile i) against the B fragments of K-step ks; a slab is NBLK blocks, K-step
+    // 0's then K-step 1's.  Block n reads the A fragment of block n + L and a
+    // share of the B fragments needed next (K-step 1's during K-step 0, the next
+    // slab's first ones in the last L blocks), and the next slab is published
+    // before the last L blocks: their MFMAs, whose operands are in registers by
+    // then, cover the latency of the next slab's first reads, which one wave per
+    // SIMD cannot hide behind another wave's work.  Fragments live in register
+    // tuples of their own, whose padding (the zero half of a block) is set once:
+    // an LDS read fills the rest, so no vector instruction touches an MFMA
+    // operand in the loop.
+    typedef typename opnd<FA>::type opa_t;
+    typedef typename opnd<FB>::type opb_t;
+    constexpr int NBLK = 2 * TM, L = TM >= 8 ? 3 : 2, RING = 4;
+    static_assert(NBLK % RING == 0 && RING > L, "A fragments ahead");
+    opb_t bf[2][TN];
+    opa_t af[RING];
+    int be[2][TN], ae[2][TM];  // by slab parity: a lane's exponents of both K-steps (groups 2 lb and 2 lb + 1)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) bf[0][j] = bf[1][j] = opb_t{};
+#pragma unroll
+    for (int q = 0; q < RING; ++q) af[q] = opa_t{};
+    const int swz6 = (lr >> 1) & 7, swz4 = (lr >> 2) & 3;
+    const int a_r = wr * CF::WM + lr, b_r = wc * CF::WN + lr;
+    constexpr int ER = XP ? 16 : CF::EK;  // exponent bytes per row
+    const int ea_lane = (XP ? 0 : CF::OFF_EA) + a_r * ER + 2 * lb;
+    const int eb_lane = (XP ? 16 * CF::BM : CF::OFF_EB) + b_r * ER + 2 * lb;
+    auto slot_addr = [&](int plane_off, int fp4, int r, int t, int ks) {
+      return fp4 ? plane_off + (r + 16 * t) * 64 + ((lb ^ swz4) * 16)
+                 : plane_off + (r + 16 * t) * 128 + (((2 * lb + ks) ^ swz6) * 16);
+    };
+    // An operand's registers from its LDS slot (the rules of op_a / op_b): FP6,
+    // the slot's 16 bytes below two zero registers; FP4 against FP4, A's pair as
+    // read and B's active group in its half of a zeroed block; FP4 against FP6,
+    // the active group in half 0 (the other operand's half 1 is zero).
+    auto fill_a = [&](opa_t& v, const uint8_t* st, int i, int ks) {
+      const uint8_t* p = st + slot_addr(0, FA, a_r, i, ks);
+      if constexpr (!FA || FB) {
+        const v4i x = *reinterpret_cast<const v4i*>(p);
+        v[0] = x[0], v[1] = x[1], v[2] = x[2], v[3] = x[3];
+      } else {
+        const v2i x = *reinterpret_cast<const v2i*>(p + 8 * ks);
+        v[0] = x[0], v[1] = x[1];
+      }
+    };
+    auto fill_b = [&](opb_t& v, const uint8_t* st, int j, int ks) {
+      const uint8_t* p = st + slot_addr(CF::OFF_B, FB, b_r, j, ks);
+      if constexpr (!FB) {
+        const v4i x = *reinterpret_cast<const v4i*>(p);
+        v[0] = x[0], v[1] = x[1], v[2] = x[2], v[3] = x[3];
+      } else {
+        const v2i x = *reinterpret_cast<const v2i*>(p + 8 * ks);
+        if (FA && ks) v[2] = x[0], v[3] = x[1];
+        else v[0] = x[0], v[1] = x[1];
+      }
+    };
+    auto publish = [&]() {
+      // every direct load and LDS access of this wave has landed
+      __builtin_amdgcn_s_waitcnt(0);
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    };
+    // The next slab's loads in NPART parts, one per block: the first L in the
+    // last blocks of the slab before it (behind the barrier that frees its
+    // stage), the others from block 0 on.
+    constexpr int NPART = NLOAD < FASTBFP_MX_SPREAD ? NLOAD : FASTBFP_MX_SPREAD;
+    constexpr int EARLY = L < NPART ? L : NPART;
+    // PAR: the slab's parity.  cur / xcur, nxt / xnxt: its stage and exponents,
+    // and the next slab's; xload, xload2: where the exponents of the next slab
+    // and of the one after it go (null: with another slab's).
+    auto step = [&](auto parc, const uint8_t* cur, uint8_t* curw, uint8_t* nxt, int s, const uint8_t* xcur,
+                    const uint8_t* xnxt, int hnxt, uint8_t* xload, uint8_t* xload2) __attribute__((always_inline)) {
+      constexpr int PAR = decltype(parc)::value;
+      static_for<NBLK>([&](auto bc) __attribute__((always_inline)) {
+        constexpr int n = decltype(bc)::value, ks = n / TM, i = n % TM;
+        if constexpr (n == NBLK - L) {
+          put_exps(nxt, e_regs);
+          __builtin_amdgcn_sched_barrier(0);
+          publish();
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (FA && FB && n == TM) asm volatile("" ::: "memory");  // (A's pair slots are read again)
+        auto rd16 = [&](const uint8_t* x, int off) { return (int)*reinterpret_cast<const uint16_t*>(x + off); };
+        // the A fragment of block n + L
+        if constexpr (n + L < NBLK) {
+          constexpr int m = n + L;
+          fill_a(af[m % RING], cur, m % TM, m / TM);
+          if constexpr (m < TM) ae[PAR][m] = rd16(xcur, ea_lane + (XP ? 8 * (PAR) : 0) + m * 16 * ER);
+        } else {
+          constexpr int m = n + L - NBLK;
+          fill_a(af[m % RING], nxt, m, 0);
+          ae[PAR ^ 1][m] = rd16(xnxt, ea_lane + hnxt + m * 16 * ER);
+        }
+        // B: K-step 1's share, or the next slab's first ones
+        if constexpr (ks == 0) {
+#pragma unroll
+          for (int j = n * TN / TM; j < (n + 1) * TN / TM; ++j) fill_b(bf[1][j], cur, j, 1);
+        }
+        if constexpr (n >= NBLK - L && n < NBLK - 1) {
+          constexpr int q = n - (NBLK - L);
+#pragma unroll
+          for (int j = q * TN / (L - 1); j < (q + 1) * TN / (L - 1); ++j) {
+            fill_b(bf[0][j], nxt, j, 0);
+            be[PAR ^ 1][j] = rd16(xnxt, eb_lane + hnxt + j * 16 * ER);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          if (j == 0)
+            mma_held<FA, FB, ks, (TM < 8 || TN < 8)>(acc[i][j], af[n % RING], bf[ks][j], ae[PAR][i], be[PAR][j]);
+          else
+            mma_held<FA, FB, ks, false>(acc[i][j], af[n % RING], bf[ks][j], ae[PAR][i], be[PAR][j]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (n < NPART - EARLY) {
+          const bool more = s + 1 < nslabs;
+          issue(nxt, more ? s + 1 : s, more, e_regs, xload, EARLY + n, NPART);
+        }
+        if constexpr (n >= NBLK - L && n - (NBLK - L) < EARLY) {
+          const bool more = s + 2 < nslabs;
+          issue(curw, more ? s + 2 : s, more, e_regs, xload2, n - (NBLK - L), NPART);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    if (nslabs > 0) {
+      // slab 0 was issued above; publish it, start slab 1, and read the first
+      // fragments
+      publish();
+      {
+        if (1 < nslabs) {
+#pragma unroll
+          for (int q = 0; q < EARLY; ++q) issue(stage1, 1, true, e_regs, nullptr, q, NPART);
+        }
+      }
+      const uint8_t* x0 = XP ? xe0 : stage0;
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        fill_b(bf[0][j], stage0, j, 0);
+        be[0][j] = (int)*reinterpret_cast<const uint16_t*>(x0 + eb_lane + j * 16 * ER);
+      }
+#pragma unroll
+      for (int m = 0; m < L; ++m) {
+        fill_a(af[m], stage0, m, 0);
+        ae[0][m] = (int)*reinterpret_cast<const uint16_t*>(x0 + ea_lane + m * 16 * ER);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // (Drained at the end of every loop iteration: where tiles leave accumulator
+    // registers free, the register allocator moves accumulators between
+    // registers on the edges of the loop.)
+    int s = 0;
+    if constexpr (XP) {
+      // Unrolled by four: slab s in stage s % 2, its exponents in half s % 2 of
+      // xe[(s / 2) % 2], loaded with slab s & ~1.
+      auto one = [&](auto kc) __attribute__((always_inline)) {
+        constexpr int k = decltype(kc)::value;
+        uint8_t* c = k & 1 ? stage1 : stage0;
+        uint8_t* x = k & 1 ? stage0 : stage1;
+        uint8_t* xc = (k / 2) & 1 ? xe1 : xe0;
+        uint8_t* xn = ((k + 1) / 2) & 1 ? xe1 : xe0;
+        uint8_t* xn2 = ((k + 2) / 2) & 1 ? xe1 : xe0;
+        step(ic<(k & 1)>{}, c, c, x, s + k, xc, xn, 8 * ((k + 1) & 1), (k + 1) & 1 ? nullptr : xn,
+             k & 1 ? nullptr : xn2);
+      };
+      for (; s + 4 <= nslabs; s += 4) {
+        one(ic<0>{});
+        one(ic<1>{});
+        one(ic<2>{});
+        one(ic<3>{});
+        mma_drain(acc);
+      }
+      if (s < nslabs) {
+        one(ic<0>{});
+        mma_drain(acc);
+      }
+      if (s + 1 < nslabs) {
+        one(ic<1>{});
+        mma_drain(acc);
+      }
+      if (s + 2 < nslabs) {
+        one(ic<2>{});
+        mma_drain(acc);
+      }
+    } else {
+      for (; s + 2 <= nslabs; s += 2) {
+        step(ic<0>{}, stage0, stage0, stage1, s, stage0, stage1, 0, nullptr, nullptr);
+        step(ic<1>{}, stage1, stage1, stage0, s + 1, stage1, stage0, 0, nullptr, nullptr);
+        mma_drain(acc);
+      }
+      if (s < nslabs) {
+        step(ic<0>{}, stage0, stage0, stage1, s, stage0, stage1, 0, nullptr, nullptr);
+        mma_drain(acc);
+      }
+    }
+  } else {
   // One slab: publish slab s (its direct loads and exponent writes, from
   // every wave), start the loads of slab s + 1 into the other stage (which
   // held slab s - 1, finished by every wave), compute slab s, then write the
@@ -734,57 +976,7 @@ __global__ __launch_bounds__(CF::NT) void k_gemm_mx(const uint8_t* __restrict__ 
       const u32x4 y = rd(slot_addr(plane_off, 0, r, t, 1));
       return v8i{(int)x[0], (int)x[1], (int)x[2], (int)y[0], (int)y[1], (int)y[2], 0, 0};
     };
-    if constexpr (CF::PIPE) {
-      // Software pipeline.  A block is the TN MFMAs of one A fragment (row
-      // tile i) against the B fragments of K-step ks; a phase is one K-step,
-      // TM blocks.  Each block reads the next block's A fragment and a share
-      // of the next phase's B fragments, and a scheduling barrier closes it,
-      // so that about two blocks' fragments are live at a time.
-      constexpr int BPP = TM;           // blocks per phase
-      constexpr int NPH = CF::KSTEPS;   // phases per slab
-      v8i bf[2][TN], af[2];
-      // A lane's exponents of both K-steps (groups 2 lb and 2 lb + 1) are
-      // adjacent bytes: one 16-bit read per fragment in the first phase, and
-      // each MFMA takes its K-step's byte of it as the block scale.
-      int be[TN], ae[TM];
-      auto rd16 = [&](int off) { return (int)*reinterpret_cast<const uint16_t*>(xcur + off); };
-      auto read_b = [&](int ks, int j) {
-        bf[ks & 1][j] = op_b<FA, FB>(rd(slot_addr(CF::OFF_B, FB, b_r, j, ks)), ks);
-        if (ks == 0) be[j] = rd16(eb_lane + j * 16 * ER);
-      };
-      auto read_a = [&](int blk) {
-        const int ks = blk / BPP, i = blk % BPP;
-        af[blk & 1] = op_a<FA, FB>(rd(slot_addr(0, FA, a_r, i, ks)), ks);
-        if (ks == 0) ae[i] = rd16(ea_lane + i * 16 * ER);
-      };
-#pragma unroll
-      for (int j = 0; j < TN; ++j) read_b(0, j);
-      read_a(0);
-      // An FP4 slot serves both K-steps; the empty asm statements (here and
-      // at the phase boundary) keep the compiler from merging the two phases'
-      // reads of it, which would hold every raw fragment for the whole slab.
-      if constexpr ((FA || FB) && NPH == 2) asm volatile("" ::: "memory");
-#pragma unroll
-      for (int blk = 0; blk < NPH * BPP; ++blk) {
-        const int ph = blk / BPP, bi = blk % BPP, i = blk % TM;
-        if constexpr ((FA || FB) && NPH == 2)
-          if (blk == BPP) asm volatile("" ::: "memory");
-        if (blk + 1 < NPH * BPP) read_a(blk + 1);
-        if (ph + 1 < NPH) {
-#pragma unroll
-          for (int j = bi * TN / BPP; j < (bi + 1) * TN / BPP; ++j) read_b(ph + 1, j);
-        }
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          if (ph == 0)
-            mma<FA, FB, 0, 0>(acc[i][j], af[blk & 1], bf[0][j], ae[i], be[j]);
-          else
-            mma<FA, FB, 1, 1>(acc[i][j], af[blk & 1], bf[1][j], ae[i], be[j]);
-        }
-        issue_after(blk, NPH * BPP);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    } else if constexpr (CF::G == 32) {
+    if constexpr (CF::G == 32) {
       // Compiler-scheduled, one K-step: per B chunk the B fragments, then each
       // A fragment against them.
       static_for<NB>([&](auto cbc) {
@@ -1060,6 +1252,7 @@ __global__ __launch_bounds__(CF::NT) void k_gemm_mx(const uint8_t* __restrict__ 
     }
     if (s < nslabs) step(stage0, stage1, s, stage0, nullptr, 0);
   }
+  }
   mma_drain(acc);
 
   // Epilogue: lane holds row lr, columns 4*lb .. 4*lb + 3 of each 16x16
@@ -1067,6 +1260,43 @@ __global__ __launch_bounds__(CF::NT) void k_gemm_mx(const uint8_t* __restrict__ 
   // C's rows are 16-byte aligned and the four columns exist.
   if constexpr (QNCH == 0) {
     const bool vec = (ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0;
+    const int wcol = col0 + wc * CF::WN;
+    if (TN % 2 == 0 && vec && wcol + CF::WN <= N) {
+      // The wave's columns all exist: pairs of 16-column tiles, lanes r and r +
+      // 8 of a lane block exchanging halves, so that a store instruction writes
+      // 8 rows x 128 bytes, whole lines, which can bypass the caches (a C of
+      // hundreds of MB does not stay in them, and pushes out the operand
+      // panels).  As 16 rows x 64 bytes through L2, C cost 13 us per round of
+      // 256 x 256 tiles.  Measured: ffn_up (4,4) 686 -> 629 us, (6,6) 1313 ->
+      // 1242; 802816 x 64 x 576 (2,2) 137 -> 92; 802816 x 576 x 64 413 -> 323;
+      // whole lines through L2 instead: 647, 1320, 130; half lines past the
+      // caches: 678, 1269, 98 and 558.  The sums of a product's parts stay in the
+      // caches: they are read back at once.
+      const int r8 = lr & 7, dc = (lr & 8) * 2 + 4 * lb;
+      auto store = [&](auto ntc) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          const int row = row0 + wr * CF::WM + i * 16 + r8;
+          float* p = C + (int64_t)row * ldc + wcol + dc;
+#pragma unroll
+          for (int j = 0; j + 1 < TN; j += 2) {
+            v4f x, y;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+              const int lo = __float_as_int(acc[i][j][t] * scale), hi = __float_as_int(acc[i][j + 1][t] * scale);
+              // row_ror:8 into the upper, then the lower eight lanes of each sixteen
+              x[t] = __int_as_float(__builtin_amdgcn_update_dpp(lo, hi, 0x128, 0xF, 0xC, false));
+              y[t] = __int_as_float(__builtin_amdgcn_update_dpp(hi, lo, 0x128, 0xF, 0x3, false));
+            }
+            if (row < M) put<v4f, decltype(ntc)::value != 0>(reinterpret_cast<v4f*>(p + 16 * j), x);
+            if (row + 8 < M) put<v4f, decltype(ntc)::value != 0>(reinterpret_cast<v4f*>(p + 8 * ldc + 16 * j), y);
+          }
+        }
+      };
+      if (part_slabs > 0) store(ic<0>{});
+      else store(ic<1>{});
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       const int row = row0 + wr * CF::WM + i * 16 + lr;
