@@ -39,8 +39,11 @@
 // load instruction still reads whole runs of consecutive rows.  With full
 // slabs of groups of 16, the exponents of two slabs come in one 16-byte load
 // per row into a buffer of their own.  Slabs are double buffered in two LDS
-// objects: the loads of slab s+1 are issued right after the barrier that
-// publishes slab s and have all of slab s's MFMAs to land.  Every load
+// objects.  The one-chunk kernels and those with an operand split at 2 bits
+// publish slab s+1 a few blocks of MFMAs before slab s ends and read its first
+// fragments while slab s's last blocks run, so that the matrix cores do not
+// stand still at the barrier; the others issue the loads of slab s+1 right
+// after the barrier that publishes slab s.  Every load
 // instruction costs the MFMA waves that issue it time, so the kernel issues
 // no load it does not need (an L2 prefetch of slab s+2 cost more than it
 // saved) and spreads a slab's loads between blocks of MFMAs.  A 256-thread
@@ -893,6 +896,254 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
         mma_drain(acc);
       }
     }
+  } else if constexpr (COMB) {
+    // An operand split at 2 bits (q = 4 (q >> 2) + (q & 3)) fills a whole
+    // 32-value MFMA block with one group of 16: the codes of +-(q >> 2)/2 (its
+    // FP6 plane) in half 0 and those of +-(q & 3)/8 (its Lo2 plane, unpacked) in
+    // half 1, i.e. q/8 per value.  The other operand's group is repeated in both
+    // halves, one block per chunk plane of it.  So a fragment pair takes one
+    // MFMA per chunk plane of the repeated operand and no block holds zeros:
+    // (6,6) 2 MFMAs per group of 16 where separate chunk passes over half-empty
+    // blocks take 4, (6, m <= 4) 1 where they take 2.  The combined operand C is
+    // A when A is split at 2 bits, else B; D is the other.  The scale bytes carry
+    // the chunk weights: 2 for the combined block (q/8 against the unit q/2) on
+    // C's side plus the repeated plane's on D's.
+    //
+    // The pipeline is the one-chunk kernel's (above): a block is one C fragment
+    // against every D fragment and plane, block n reads the slots of C's block n
+    // + L and a share of D's next K-step, and the next slab is published L blocks
+    // early.  What has to be built with vector instructions (C's unpacked lower
+    // half, D's second copy) is built a block ahead, in the shadow of this
+    // block's MFMAs, in the tuples that the LDS reads fill.  Against reading each
+    // slab's first fragments after its barrier and building D's copies between the
+    // K-steps, 8192 x 16384 x 4096: (6,6) 1330 -> 1240 us, (6,4) 1230 -> 1123, (6,2)
+    // 917 -> 857, (6,8) 2262 -> 1909; 2048^3 (6,6) 42 -> 39.5.
+    constexpr bool CA = NA == 2 && FA;
+    constexpr int TC = CA ? TM : TN, TD = CA ? TN : TM, ND = CA ? NB : NA;
+    constexpr int C0 = CA ? mx::a_plane<CF>(0) : mx::b_plane<CF>(0);  // FP6 plane of q >> 2
+    constexpr int C1 = CA ? mx::a_plane<CF>(1) : mx::b_plane<CF>(1);  // Lo2 plane of q & 3
+    constexpr int DP0 = CA ? mx::b_plane<CF>(0) : mx::a_plane<CF>(0);
+    constexpr int DP1 = CA ? mx::b_plane<CF>(1) : mx::a_plane<CF>(1);
+    constexpr int DF4 = (CA ? mx::b_kind<CF>(0) : mx::a_kind<CF>(0)) == kPlaneFP4;
+    constexpr int DL2 = ND == 2 && (CA ? mx::b_kind<CF>(1) : mx::a_kind<CF>(1)) == kPlaneLo2;
+    constexpr int FD = CA ? FB : FA;
+    constexpr int NBLK = 2 * TC, L = TC >= 8 ? 3 : 2, RING = 4, NE = ND * TD;
+    constexpr int RB0 = TC - 2, RB1 = L - 1;  // blocks that read D for K-step 1, and for the next slab
+    static_assert(NBLK % RING == 0 && RING > L, "C fragments ahead");
+    static_assert(NE >= 4 && RB0 >= 1 && RB1 >= 1, "D operands ahead");
+    typedef typename opnd<DF4>::type opd_t;
+    v6i cv[RING], d1[2][TD];
+    opd_t d0[2][TD];
+    v2i cl[RING], dl[TD];
+    int ce[2][TC], de[2][ND][TD], dr[TD];
+#pragma unroll
+    for (int q = 0; q < RING; ++q) cv[q] = v6i{};
+#pragma unroll
+    for (int t = 0; t < TD; ++t) {
+      d0[0][t] = d0[1][t] = opd_t{};
+      d1[0][t] = d1[1][t] = v6i{};
+    }
+    const int swz6 = (lr >> 1) & 7, swz4 = (lr >> 2) & 3;
+    const int a_r = wr * CF::WM + lr, b_r = wc * CF::WN + lr;
+    const int c_r = CA ? a_r : b_r, d_r = CA ? b_r : a_r;
+    constexpr int ER = XP ? 16 : CF::EK;  // exponent bytes per row
+    const int ea_lane = (XP ? 0 : CF::OFF_EA) + a_r * ER + 2 * lb;
+    const int eb_lane = (XP ? 16 * CF::BM : CF::OFF_EB) + b_r * ER + 2 * lb;
+    const int c_e = CA ? ea_lane : eb_lane, d_e = CA ? eb_lane : ea_lane;
+    auto slot6 = [&](int off, int r, int t, int ks) { return off + (r + 16 * t) * 128 + (((2 * lb + ks) ^ swz6) * 16); };
+    auto slot4 = [&](int off, int r, int t, int ks) { return off + (r + 16 * t) * 64 + ((lb ^ swz4) * 16) + 8 * ks; };
+    auto rd128 = [&](auto& v, const uint8_t* q) {
+      const v4i x = *reinterpret_cast<const v4i*>(q);
+      v[0] = x[0], v[1] = x[1], v[2] = x[2], v[3] = x[3];
+    };
+    auto rd16 = [&](const uint8_t* x, int off) { return (int)*reinterpret_cast<const uint16_t*>(x + off); };
+    // Block m's C slots, and its exponents (of both K-steps, with K-step 0).
+    auto read_c = [&](const uint8_t* st, const uint8_t* x, int half, int m, int par) __attribute__((always_inline)) {
+      const int ks = m / TC, c = m % TC;
+      rd128(cv[m % RING], st + slot6(C0, c_r, c, ks));
+      cl[m % RING] = *reinterpret_cast<const v2i*>(st + slot4(C1, c_r, c, ks));
+      if (ks == 0) ce[par][c] = rd16(x, c_e + half + c * 16 * ER);
+    };
+    auto build_c = [&](int m, int par) __attribute__((always_inline)) {
+      uint32_t t0, t1, t2;
+      lo2_unpack((uint32_t)cl[m % RING][0], (uint32_t)cl[m % RING][1], t0, t1, t2);
+      v6i& v = cv[m % RING];
+      v[3] = (int)t0, v[4] = (int)t1, v[5] = (int)t2;
+      if (m / TC == 0) ce[par][m % TC] += 0x0202;  // (both K-steps' bytes stay below 256 for exponents up to 250)
+    };
+    // Entry e of D's NE = ND TD (plane, fragment) operands of K-step ks.
+    auto read_d = [&](const uint8_t* st, const uint8_t* x, int half, int e, int ks) __attribute__((always_inline)) {
+      const int pl = e / TD, t = e % TD;
+      if (pl == 0) {
+        if constexpr (DF4) {
+          const v2i y = *reinterpret_cast<const v2i*>(st + slot4(DP0, d_r, t, ks));
+          d0[ks][t][0] = y[0], d0[ks][t][1] = y[1];
+        } else {
+          rd128(d0[ks][t], st + slot6(DP0, d_r, t, ks));
+        }
+        if (ks == 0) dr[t] = rd16(x, d_e + half + t * 16 * ER);
+      } else if constexpr (DL2) {
+        dl[t] = *reinterpret_cast<const v2i*>(st + slot4(DP1, d_r, t, ks));
+      } else {
+        rd128(d1[ks][t], st + slot6(DP1, d_r, t, ks));
+      }
+    };
+    auto build_d = [&](int e, int ks, int par) __attribute__((always_inline)) {
+      const int pl = e / TD, t = e % TD;
+      if (pl == 0) {
+        if constexpr (DF4) {
+          d0[ks][t][2] = d0[ks][t][0], d0[ks][t][3] = d0[ks][t][1];
+        } else {
+          d0[ks][t][3] = d0[ks][t][0], d0[ks][t][4] = d0[ks][t][1], d0[ks][t][5] = d0[ks][t][2];
+        }
+        if (ks == 0) {
+          de[par][0][t] = dr[t] + 0x0101 * mx::plane_weight<ND, FD>(0);
+          if constexpr (ND == 2) de[par][ND - 1][t] = dr[t] + 0x0101 * mx::plane_weight<ND, FD>(1);
+        }
+      } else {
+        v6i& v = d1[ks][t];
+        if constexpr (DL2) {
+          uint32_t t0, t1, t2;
+          lo2_unpack((uint32_t)dl[t][0], (uint32_t)dl[t][1], t0, t1, t2);
+          v[0] = (int)t0, v[1] = (int)t1, v[2] = (int)t2;
+        }
+        v[3] = v[0], v[4] = v[1], v[5] = v[2];
+      }
+    };
+    auto publish = [&]() {
+      __builtin_amdgcn_s_waitcnt(0);
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    };
+    constexpr int NPART = NLOAD < FASTBFP_MX_SPREAD ? NLOAD : FASTBFP_MX_SPREAD;
+    constexpr int EARLY = L < NPART ? L : NPART;
+    // One load part per block from block 0 on needs NPART - EARLY blocks; with
+    // few blocks two go together.
+    constexpr int PER = NPART - EARLY > NBLK - L - 2 ? 2 : 1;
+    static_assert(NPART - EARLY <= PER * (NBLK - L), "the loads end before the slab is published");
+    auto step = [&](auto parc, const uint8_t* cur, uint8_t* curw, uint8_t* nxt, int s, const uint8_t* xcur, int hcur,
+                    const uint8_t* xnxt, int hnxt, uint8_t* xload, uint8_t* xload2) __attribute__((always_inline)) {
+      constexpr int PAR = decltype(parc)::value;
+      static_for<NBLK>([&](auto bc) __attribute__((always_inline)) {
+        constexpr int n = decltype(bc)::value, ks = n / TC, c = n % TC;
+        if constexpr (n == NBLK - L) {
+          put_exps(nxt, e_regs);
+          __builtin_amdgcn_sched_barrier(0);
+          publish();
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (n + L < NBLK) read_c(cur, xcur, hcur, n + L, PAR);
+        else read_c(nxt, xnxt, hnxt, n + L - NBLK, PAR ^ 1);
+        if constexpr (n < RB0) {
+#pragma unroll
+          for (int e = n * NE / RB0; e < (n + 1) * NE / RB0; ++e) read_d(cur, xcur, hcur, e, 1);
+        }
+        if constexpr (n >= NBLK - L && n - (NBLK - L) < RB1) {
+          constexpr int q = n - (NBLK - L);
+#pragma unroll
+          for (int e = q * NE / RB1; e < (q + 1) * NE / RB1; ++e) read_d(nxt, xnxt, hnxt, e, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // D entries read in the block before are completed in this one
+        constexpr bool B0 = n >= 1 && n - 1 < RB0, B1 = n - 1 >= NBLK - L && n - 1 - (NBLK - L) < RB1;
+        constexpr int q1 = n - 1 - (NBLK - L);
+        constexpr int e0 = B0 ? (n - 1) * NE / RB0 : B1 ? q1 * NE / RB1 : 0;
+        constexpr int e1 = B0 ? n * NE / RB0 : B1 ? (q1 + 1) * NE / RB1 : 0;
+        constexpr int bks = B0 ? 1 : 0, bpar = B0 ? PAR : PAR ^ 1;
+        static_for<NE>([&](auto mc) __attribute__((always_inline)) {
+          constexpr int k = decltype(mc)::value, pl = k / TD, t = k % TD;
+          auto go = [&](const auto& d) __attribute__((always_inline)) {
+            if constexpr (CA)
+              mma_held<0, (pl == 0 && DF4), ks, false>(acc[c][t], cv[n % RING], d, ce[PAR][c], de[PAR][pl][t]);
+            else
+              mma_held<(pl == 0 && DF4), 0, ks, false>(acc[t][c], d, cv[n % RING], de[PAR][pl][t], ce[PAR][c]);
+          };
+          if constexpr (pl == 0) go(d0[ks][t]);
+          else go(d1[ks][t]);
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (k == 1) build_c((n + 1) % NBLK, n + 1 < NBLK ? PAR : PAR ^ 1);
+          if constexpr (k >= 1 && k <= NE - 3) {
+            // (the last two MFMAs keep vector writes away from the next block's operands)
+#pragma unroll
+            for (int e = e0 + (k - 1) * (e1 - e0) / (NE - 3); e < e0 + k * (e1 - e0) / (NE - 3); ++e)
+              build_d(e, bks, bpar);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        });
+        static_for<PER>([&](auto pc) __attribute__((always_inline)) {
+          constexpr int q = EARLY + n * PER + decltype(pc)::value;
+          if constexpr (q < NPART) {
+            const bool more = s + 1 < nslabs;
+            issue(nxt, more ? s + 1 : s, more, e_regs, xload, q, NPART);
+          }
+        });
+        if constexpr (n >= NBLK - L && n - (NBLK - L) < EARLY) {
+          const bool more = s + 2 < nslabs;
+          issue(curw, more ? s + 2 : s, more, e_regs, xload2, n - (NBLK - L), NPART);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    if (nslabs > 0) {
+      publish();
+      if (1 < nslabs) {
+#pragma unroll
+        for (int q = 0; q < EARLY; ++q) issue(stage1, 1, true, e_regs, nullptr, q, NPART);
+      }
+      const uint8_t* x0 = XP ? xe0 : stage0;
+#pragma unroll
+      for (int m = 0; m < L; ++m) read_c(stage0, x0, 0, m, 0);
+#pragma unroll
+      for (int e = 0; e < NE; ++e) read_d(stage0, x0, 0, e, 0);
+      build_c(0, 0);
+#pragma unroll
+      for (int e = 0; e < NE; ++e) build_d(e, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_nop 1" ::: "memory");
+    }
+    int s = 0;
+    if constexpr (XP) {
+      auto one = [&](auto kc) __attribute__((always_inline)) {
+        constexpr int k = decltype(kc)::value;
+        uint8_t* c = k & 1 ? stage1 : stage0;
+        uint8_t* x = k & 1 ? stage0 : stage1;
+        uint8_t* xc = (k / 2) & 1 ? xe1 : xe0;
+        uint8_t* xn = ((k + 1) / 2) & 1 ? xe1 : xe0;
+        uint8_t* xn2 = ((k + 2) / 2) & 1 ? xe1 : xe0;
+        step(ic<(k & 1)>{}, c, c, x, s + k, xc, 8 * (k & 1), xn, 8 * ((k + 1) & 1), (k + 1) & 1 ? nullptr : xn,
+             k & 1 ? nullptr : xn2);
+      };
+      for (; s + 4 <= nslabs; s += 4) {
+        one(ic<0>{});
+        one(ic<1>{});
+        one(ic<2>{});
+        one(ic<3>{});
+        mma_drain(acc);
+      }
+      if (s < nslabs) {
+        one(ic<0>{});
+        mma_drain(acc);
+      }
+      if (s + 1 < nslabs) {
+        one(ic<1>{});
+        mma_drain(acc);
+      }
+      if (s + 2 < nslabs) {
+        one(ic<2>{});
+        mma_drain(acc);
+      }
+    } else {
+      for (; s + 2 <= nslabs; s += 2) {
+        step(ic<0>{}, stage0, stage0, stage1, s, stage0, 0, stage1, 0, nullptr, nullptr);
+        step(ic<1>{}, stage1, stage1, stage0, s + 1, stage1, 0, stage0, 0, nullptr, nullptr);
+        mma_drain(acc);
+      }
+      if (s < nslabs) {
+        step(ic<0>{}, stage0, stage0, stage1, s, stage0, 0, stage1, 0, nullptr, nullptr);
+        mma_drain(acc);
+      }
+    }
   } else {
   // One slab: publish slab s (its direct loads and exponent writes, from
   // every wave), start the loads of slab s + 1 into the other stage (which
@@ -1000,110 +1251,6 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
             issue_after((cb * NA + ca) * TM + i, NB * NA * TM);
           }
         });
-      });
-    } else if constexpr (COMB) {
-      // An operand split at 2 bits (q = 4 (q >> 2) + (q & 3)) fills a whole
-      // 32-value MFMA block with one group of 16: the codes of +-(q >> 2)/2
-      // (its FP6 plane) in half 0 and those of +-(q & 3)/8 (its Lo2 plane,
-      // unpacked) in half 1, i.e. q/8 per value.  The other operand's group
-      // is repeated in both halves, one block per chunk plane of it.  So a
-      // fragment pair takes one MFMA per chunk plane of the repeated operand
-      // and no block holds zeros: (6,6) 2 MFMAs per group of 16 where
-      // separate chunk passes over half-empty blocks take 4, (6, m <= 4) 1
-      // where they take 2.  The combined operand C is A when A is split at 2
-      // bits, else B; D is the other.  The scale bytes carry the chunk
-      // weights: 2 for the combined block (q/8 against the unit q/2) plus the
-      // repeated plane's.
-      //
-      // Software pipeline: a block is one C fragment (K-step ks, fragment c)
-      // against every D fragment and plane (TD * ND MFMAs).  Each block first
-      // reads the next block's C slots (a Lo2 slot holds both K-steps' groups
-      // and is read once), and the blocks of K-step 0 read a share of K-step
-      // 1's D slots; D's repeated operands are built from the raw slots at
-      // the start of each K-step; a scheduling barrier closes each block.
-      constexpr bool CA = NA == 2 && FA;
-      constexpr int TC = CA ? TM : TN, TD = CA ? TN : TM, ND = CA ? NB : NA;
-      constexpr int C0 = CA ? mx::a_plane<CF>(0) : mx::b_plane<CF>(0);  // FP6 plane of q >> 2
-      constexpr int C1 = CA ? mx::a_plane<CF>(1) : mx::b_plane<CF>(1);  // Lo2 plane of q & 3
-      constexpr int DP0 = CA ? mx::b_plane<CF>(0) : mx::a_plane<CF>(0);
-      constexpr int DP1 = CA ? mx::b_plane<CF>(1) : mx::a_plane<CF>(1);
-      constexpr int DK0 = CA ? mx::b_kind<CF>(0) : mx::a_kind<CF>(0);
-      constexpr int DK1 = CA ? mx::b_kind<CF>(1) : mx::a_kind<CF>(1);
-      constexpr int FD = CA ? FB : FA;
-      const int c_r = CA ? a_r : b_r, d_r = CA ? b_r : a_r;
-      const int c_e = CA ? ea_lane : eb_lane, d_e = CA ? eb_lane : ea_lane;
-      u32x4 dr[2][ND][TD];  // D's raw slots per K-step (an FP4 / Lo2 slot only in [0])
-      int de[TD];
-      v8i dd[ND][TD];       // D's repeated operands of the current K-step
-      u32x4 ch[2], cl[TC];  // C's FP6 slots (per block) and Lo2 slots (per fragment)
-      // Exponents: both K-steps' bytes of a fragment in one 16-bit read (in
-      // K-step 0); each MFMA takes its K-step's byte (the weights added to
-      // both bytes stay below 256 for exponents up to 250).
-      int ce[TC];
-      auto rd16 = [&](int off) { return (int)*reinterpret_cast<const uint16_t*>(xcur + off); };
-      auto read_d = [&](int ks, int t) {
-        static_for<ND>([&](auto pc) {
-          constexpr int p = decltype(pc)::value, k = p == 0 ? DK0 : DK1, off = p == 0 ? DP0 : DP1;
-          if (k == kPlaneFP6 || ks == 0) dr[k == kPlaneFP6 ? ks : 0][p][t] = rd(slot_addr(off, k != kPlaneFP6, d_r, t, ks));
-        });
-        if (ks == 0) de[t] = rd16(d_e + t * 16 * ER);
-      };
-      auto read_c = [&](int blk) {
-        const int ks = blk / TC, c = blk % TC;
-        ch[blk & 1] = rd(slot_addr(C0, 0, c_r, c, ks));
-        if (ks == 0) {
-          cl[c] = rd(slot_addr(C1, 1, c_r, c, 0));
-          ce[c] = rd16(c_e + c * 16 * ER);
-        }
-      };
-      // the group repeated in both halves, from a raw slot of a plane of kind k
-      auto make_dup = [&](int k, const u32x4& x, int ks) -> v8i {
-        if (k == kPlaneFP6) return v8i{(int)x[0], (int)x[1], (int)x[2], (int)x[0], (int)x[1], (int)x[2], 0, 0};
-        if (k == kPlaneFP4)
-          return v8i{(int)x[2 * ks], (int)x[2 * ks + 1], (int)x[2 * ks], (int)x[2 * ks + 1], 0, 0, 0, 0};
-        uint32_t t0, t1, t2;
-        lo2_unpack(x[2 * ks], x[2 * ks + 1], t0, t1, t2);
-        return v8i{(int)t0, (int)t1, (int)t2, (int)t0, (int)t1, (int)t2, 0, 0};
-      };
-#pragma unroll
-      for (int t = 0; t < TD; ++t) read_d(0, t);
-      read_c(0);
-      static_for<2 * TC>([&](auto bc) {
-        constexpr int blk = decltype(bc)::value, ks = blk / TC, c = blk % TC;
-        if constexpr (c == 0) {
-#pragma unroll
-          for (int t = 0; t < TD; ++t)
-            static_for<ND>([&](auto pc) {
-              constexpr int p = decltype(pc)::value, k = p == 0 ? DK0 : DK1;
-              dd[p][t] = make_dup(k, dr[k == kPlaneFP6 ? ks : 0][p][t], ks);
-            });
-        }
-        if constexpr (blk + 1 < 2 * TC) read_c(blk + 1);
-        if constexpr (ks == 0) {
-#pragma unroll
-          for (int t = c * TD / TC; t < (c + 1) * TD / TC; ++t) read_d(1, t);
-        }
-        uint32_t t0, t1, t2;
-        lo2_unpack(cl[c][2 * ks], cl[c][2 * ks + 1], t0, t1, t2);
-        const u32x4& h = ch[blk & 1];
-        const v8i cv = v8i{(int)h[0], (int)h[1], (int)h[2], (int)t0, (int)t1, (int)t2, 0, 0};
-        const int e_c = ce[c];
-        // plane-major: consecutive MFMAs accumulate into different tiles
-        static_for<ND>([&](auto pc) {
-          constexpr int p = decltype(pc)::value;
-          constexpr int W = 2 + mx::plane_weight<ND, FD>(p);
-          constexpr int dfp4 = (p == 0 ? DK0 : DK1) == kPlaneFP4;
-          constexpr int W1 = 0x0101 * ((W + 1) / 2), W0 = 0x0101 * (W / 2);  // added to both bytes
-#pragma unroll
-          for (int t = 0; t < TD; ++t) {
-            if constexpr (CA)
-              mma<0, dfp4, ks, ks>(acc[c][t], cv, dd[p][t], e_c + W1, de[t] + W0);
-            else
-              mma<dfp4, 0, ks, ks>(acc[t][c], dd[p][t], cv, de[t] + W1, e_c + W0);
-          }
-        });
-        issue_after(blk, 2 * TC);
-        __builtin_amdgcn_sched_barrier(0);
       });
     } else if constexpr (PIPE2) {
       // Software pipeline of the two-chunk kernels (an operand in two chunk
