@@ -280,6 +280,22 @@ int bfp_gemm_ws(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, const
                 int64_t ldc, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * bfp_gemm_ws_route -- which kernel bfp_gemm_ws runs a product on (section
+ * III-B) with a 256-byte aligned workspace of workspace_bytes.  Host only,
+ * nothing is launched.
+ *   tile  : the tiled kernel's workgroup tile, numbered as for bfp_gemm_tiled
+ *           (0: the operand formats' default); -1: the few-output kernel.
+ *   parts : the parts that K is taken in (1: one run over K).
+ *   rows, cols : on the few-output kernel the outputs of a workgroup, else 0.
+ * A product that K in parts would be for, but whose sums the workspace does not
+ * hold, runs as bfp_gemm runs it (on its tile).
+ * BFP_E_ARG also for M = 0 or N = 0 and for a workspace below
+ * bfp_gemm_ws_size.  For tests and tuning.
+ */
+int bfp_gemm_ws_route(int a_m_bits, int b_m_bits, int64_t M, int64_t N, int64_t K, int g, int m_a, int m_b, int packed,
+                      size_t workspace_bytes, int* tile, int* parts, int* rows, int* cols);
+
+/*
  * bfp_gemm_tiled -- bfp_gemm (the same product, section III-B) with the C tile
  * that one workgroup computes chosen by the caller instead of from the shape:
  *   tile = -1 : chosen from M and N, exactly as bfp_gemm does;

@@ -39,6 +39,8 @@ SIGNATURES = {
     "bfp_repack": (_I, [_P, _P, _I64, _I64, _I, _I, _I, _I, _P, _P, _P]),
     "bfp_gemm_ws_size": (_I, [_I, _I, _I64, _I64, _I64, _I, _I, _I, _I, ctypes.POINTER(ctypes.c_size_t)]),
     "bfp_gemm_ws_full_size": (_I, [_I, _I, _I64, _I64, _I64, _I, _I, _I, _I, ctypes.POINTER(ctypes.c_size_t)]),
+    "bfp_gemm_ws_route": (_I, [_I, _I, _I64, _I64, _I64, _I, _I, _I, _I, ctypes.c_size_t,
+                               *[ctypes.POINTER(ctypes.c_int)] * 4]),
     "bfp_gemm_bfp_ws_size": (_I, [_I, _I, _I64, _I64, _I64, _I, _I, _I, ctypes.POINTER(ctypes.c_size_t)]),
     "bfp_gemm_bfp_ws": (_I, [_P, _P, _I, _P, _P, _I, _I64, _I64, _I64, _I, _I, _I, _I, _I, _U64, _P, _P, _P, _P,
                              ctypes.c_size_t, _P]),

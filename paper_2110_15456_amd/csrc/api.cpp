@@ -443,13 +443,19 @@ int bfp_gemm_ws_size(int a_m_bits, int b_m_bits, int64_t M, int64_t N, int64_t K
   return BFP_OK;
 }
 
-// The plan of a product through bfp_gemm_ws: on the operands as the kernel will
-// read them.
-static fastbfp::GemmPlan plan_of(const WsPlan& p, int a_m, int b_m, int64_t M, int64_t N, int m_a, int m_b) {
+// The plan of a product through bfp_gemm_ws, on the operands as the kernel will
+// read them: with K in parts only where a workspace of `room` bytes holds the
+// parts' sums behind the repacked operands.
+static fastbfp::GemmPlan plan_of(const WsPlan& p, int a_m, int b_m, int64_t M, int64_t N, int m_a, int m_b,
+                                 size_t room) {
   // stored widths the kernel sees (groups of 64 keep their planes where they can)
   const int sa = p.rep_a && !(p.g_in == 64 && planes_used(a_m, m_a)) ? m_a : a_m;
   const int sb = p.rep_b && !(p.g_in == 64 && planes_used(b_m, m_b)) ? m_b : b_m;
-  return fastbfp::gemm_plan(sa, planes_used(sa, m_a), sb, planes_used(sb, m_b), M, N, p.k_out, p.g_out);
+  const int na = planes_used(sa, m_a), nb = planes_used(sb, m_b);
+  const fastbfp::GemmPlan plan = fastbfp::gemm_plan(sa, na, sb, nb, M, N, p.k_out, p.g_out);
+  if (plan.parts > 1 && (room < p.bytes || room - p.bytes < parts_bytes(plan.parts, M, N)))
+    return fastbfp::gemm_plan_whole(sa, na, nb, M, N, p.g_out);
+  return plan;
 }
 
 int bfp_gemm_ws_full_size(int a_m_bits, int b_m_bits, int64_t M, int64_t N, int64_t K, int g, int m_a, int m_b,
@@ -462,8 +468,25 @@ int bfp_gemm_ws_full_size(int a_m_bits, int b_m_bits, int64_t M, int64_t N, int6
   if (st != BFP_OK) return st;
   *bytes = p.bytes;
   if (M == 0 || N == 0) return BFP_OK;
-  const fastbfp::GemmPlan plan = plan_of(p, a_m_bits, b_m_bits, M, N, m_a, m_b);
+  const fastbfp::GemmPlan plan = plan_of(p, a_m_bits, b_m_bits, M, N, m_a, m_b, SIZE_MAX);
   if (plan.parts > 1) *bytes += parts_bytes(plan.parts, M, N);
+  return BFP_OK;
+}
+
+int bfp_gemm_ws_route(int a_m_bits, int b_m_bits, int64_t M, int64_t N, int64_t K, int g, int m_a, int m_b, int packed,
+                      size_t workspace_bytes, int* tile, int* parts, int* rows, int* cols) {
+  if (!tile || !parts || !rows || !cols) return BFP_E_ARG;
+  int st = check_gemm_shape(a_m_bits, b_m_bits, M, N, K, g, m_a, m_b);
+  if (st != BFP_OK) return st;
+  WsPlan p;
+  st = ws_plan(a_m_bits, b_m_bits, M, N, K, g, m_a, m_b, packed, &p);
+  if (st != BFP_OK) return st;
+  if (workspace_bytes < p.bytes || M == 0 || N == 0) return BFP_E_ARG;
+  const fastbfp::GemmPlan plan = plan_of(p, a_m_bits, b_m_bits, M, N, m_a, m_b, workspace_bytes);
+  *tile = plan.rm > 0 ? -1 : plan.tile;
+  *parts = plan.parts;
+  *rows = 16 * plan.rm;
+  *cols = 16 * plan.rn;
   return BFP_OK;
 }
 
@@ -522,16 +545,12 @@ int bfp_gemm_ws(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, const
     }
   }
   const int na = planes_used(a_m, m_a), nb = planes_used(b_m, m_b);
-  fastbfp::GemmPlan plan = fastbfp::gemm_plan(a_m, na, b_m, nb, M, N, p.k_out, p.g_out);
+  const fastbfp::GemmPlan plan = plan_of(p, a_m_bits, b_m_bits, M, N, m_a, m_b,
+                                         workspace && aligned(workspace, 256) ? workspace_bytes : 0);
   const int exp2 = 4 - m_a - m_b;
-  // in parts only where the workspace holds their sums
-  const bool split = plan.parts > 1 && workspace && aligned(workspace, 256) &&
-                     workspace_bytes >= p.bytes + parts_bytes(plan.parts, M, N);
-  if (!split) {
-    plan.parts = 1;
+  if (plan.parts == 1)
     return status_of(fastbfp::launch_gemm_plan(plan, am, ae, a_m, na, bm, be, b_m, nb, M, N, p.k_out, p.g_out, exp2, C,
                                                ldc, s));
-  }
   float* parts = reinterpret_cast<float*>(ws + p.bytes);
   st = status_of(fastbfp::launch_gemm_plan(plan, am, ae, a_m, na, bm, be, b_m, nb, M, N, p.k_out, p.g_out, exp2, parts,
                                            fastbfp::gemm_plan_ld(N), s));

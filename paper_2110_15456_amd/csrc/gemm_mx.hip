@@ -180,6 +180,16 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 }  // namespace
 
+// The rule above, not the tile that gemm_plan found for K in parts: such a tile
+// is priced on a share of K and on the workgroups of all parts.  Over all of K
+// (4,4) 1024 x 4096 x 16384 takes 208 us on 64 workgroups of 256 x 256 and 139 on
+// the rule's 256 of 128 x 128; 2304 x 256 x 50176 457 us on 18 of 256 x 128 and
+// 278 on the rule's 72 of 128 x 64.
+GemmPlan gemm_plan_whole(int a_m, int na, int nb, int64_t M, int64_t N, int g) {
+  const bool one = na == 1 && nb == 1 && g == 16;
+  return GemmPlan{one ? gemm_mx11_tile(M, N, fmt_flag(a_m, na), false) : 0, 0, 1, 0, 0};
+}
+
 // The plan of a product that has a workspace.  A product whose tiles fill the
 // card runs as without one.  With fewer tiles, a tile's serial run of K slabs
 // sets the time (dW of ResNet-18's conv2_x, 576 x 64 x 802816, has 5 tiles of
@@ -199,8 +209,8 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 GemmPlan gemm_plan(int a_m, int na, int b_m, int nb, int64_t M, int64_t N, int64_t K, int g) {
   const int fa = fmt_flag(a_m, na), fb = fmt_flag(b_m, nb);
   const bool one = na == 1 && nb == 1 && g == 16;
-  const int rule = one ? gemm_mx11_tile(M, N, fa, false) : 0;
-  GemmPlan best{rule, 0, 1, 0, 0};
+  GemmPlan best = gemm_plan_whole(a_m, na, nb, M, N, g);
+  const int rule = best.tile;
   const int64_t slabs = ceil_div(K / 16, mx::KG);
   if (slabs == 0 || M * N > (int64_t(1) << 25)) return best;  // (at least 512 tiles of 256 x 256)
 

@@ -114,6 +114,9 @@ struct GemmPlan {
   int tile, part_slabs, parts, rm, rn;
 };
 GemmPlan gemm_plan(int a_m, int na, int b_m, int nb, int64_t M, int64_t N, int64_t K, int g);
+// The plan without room for parts: the tiled kernel in one run over K, on the
+// tile that bfp_gemm takes.
+GemmPlan gemm_plan_whole(int a_m, int na, int nb, int64_t M, int64_t N, int g);
 // Row stride of a part's matrix of N columns.
 int64_t gemm_plan_ld(int64_t N);
 // The product as planned: C (row stride ldc) is the result, or with parts > 1
