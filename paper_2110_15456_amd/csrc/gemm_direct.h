@@ -28,6 +28,7 @@ namespace direct {
 
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 constexpr int kMaxWaves = 8;
+constexpr int kMaxRowTiles = 65535;  // row tiles are the grid's y, which holds no more
 
 __device__ __forceinline__ rsrc_t make_rsrc(const uint8_t* p, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p), (short)0, (int)bytes, 0x00020000);
@@ -341,6 +342,7 @@ hipError_t launch_direct_t(int rm, int rn, const uint8_t* a_mant, const uint8_t*
   const int nss = (ng + 15) / 16;
   const int nw = nss < 1 ? 1 : nss > direct::kMaxWaves ? direct::kMaxWaves : nss;
   const dim3 grid((unsigned)((N + 16 * rn - 1) / (16 * rn)), (unsigned)((M + 16 * rm - 1) / (16 * rm)));
+  if (grid.y > (unsigned)direct::kMaxRowTiles) return hipErrorInvalidValue;  // (gemm_plan does not plan it)
 #define FASTBFP_DIRECT_LAUNCH(RM, RN)                                                                                 \
   if (rm == RM && rn == RN) {                                                                                         \
     if (out)                                                                                                          \

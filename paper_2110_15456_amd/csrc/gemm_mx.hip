@@ -279,6 +279,7 @@ GemmPlan gemm_plan(int a_m, int na, int b_m, int nb, int64_t M, int64_t N, int64
   double direct_us = 1e30;
   static const struct { int rm, rn; double us; } kDirect[] = {{1, 1, 1.36}, {2, 2, 2.8}, {4, 2, 4.2}};
   for (const auto& d : kDirect) {
+    if (ceil_div(M, 16 * d.rm) > direct::kMaxRowTiles) continue;  // does not fit its grid
     const double tm = (double)ceil_div(M, 16 * d.rm), tn = (double)ceil_div(N, 16 * d.rn);
     const double rows_a = M < 16 * d.rm ? M : 16 * d.rm, rows_b = N < 16 * d.rn ? N : 16 * d.rn;
     const double us = 1.5 + tm * tn * K * (rows_a * va + rows_b * vb) / 7e6 + 0.5 * d.us * per_wave;

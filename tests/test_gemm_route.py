@@ -80,6 +80,24 @@ def test_least_workspace_over_drawn_products():
     assert split > 100
 
 
+MAX_Y = 65535  # blocks in a grid's y
+
+
+@pytest.mark.parametrize("m_a,m_b", [(4, 4), (2, 2), (6, 6)])
+def test_row_tiles_fit_the_grid(m_a, m_b):
+    """Tall, narrow products: the few-output kernel's row tiles are its grid's y."""
+    few = 0
+    for rows in (16, 32, 64):
+        for M in (MAX_Y * rows, MAX_Y * rows + 1, 2 * MAX_Y * rows, 1 << 23, 1 << 25):
+            for N in (1, 4, 16):
+                for K in (16, 64, 1024):
+                    r = route(m_a, m_b, M, N, K, 16, None)
+                    if r[0] < 0:
+                        few += 1
+                        assert -(-M // r[2]) <= MAX_Y, (M, N, K, r)
+    assert few > 0
+
+
 def test_route_arguments():
     lib = _lib.load()
     out = [ctypes.byref(ctypes.c_int(0)) for _ in range(4)]

@@ -97,6 +97,38 @@ def test_converted_output(mm, shape):
             assert torch.equal(T.exp, R.exp) and torch.equal(T.mant, R.mant) and int(st.item()) == 0
 
 
+def close_to_values(C, A, B):
+    """At most one rounding per group and chunk pair, of sums bounded by sum |x| |y|."""
+    x, y = fb.dequantize(A).double(), fb.dequantize(B).double()
+    S = (x[:, None, :] * y[None, :, :]).abs().sum(2)
+    err = (C.double() - (x[:, None, :] * y[None, :, :]).sum(2)).abs()
+    assert bool((err <= (4 * (A.len // A.g) + 4) * 2.0**-24 * S).all())
+
+
+# Row tiles of 16, 32 and 64 rows up to the 65535 that the few-output kernel's grid
+# holds, and one more, which goes to a taller tile or to the tiled kernel.
+@pytest.mark.parametrize("m", [4, 6])
+@pytest.mark.parametrize("M", [65535 * 16, 65535 * 16 + 1, 65535 * 32 + 1, 65535 * 64 + 1])
+def test_tall_products(M, m):
+    gen = torch.Generator(device="cuda").manual_seed(M & 0xFFFF)
+    for N, K in ((1, 16), (2, 16), (1, 32)):
+        announce("tall %dx%dx%d m=%d" % (M, N, K, m))
+        A = fb.quantize(torch.randn((M, K), device="cuda", generator=gen), m=m)
+        B = fb.quantize(torch.randn((N, K), device="cuda", generator=gen), m=m)
+        close_to_values(fb.gemm(A, B), A, B)
+
+
+def test_tall_converted_output():
+    M, N, K = 65535 * 16 + 1, 16, 16
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    announce("tall converted %dx%dx%d" % (M, N, K))
+    A = fb.quantize(torch.randn((M, K), device="cuda", generator=gen), m=4)
+    B = fb.quantize(torch.randn((N, K), device="cuda", generator=gen), m=4)
+    T, R = fb.gemm_bfp(A, B, 4, rounding="stochastic", seed=5), fb.quantize(fb.gemm(A, B), m=4, rounding="stochastic",
+                                                                            seed=5)
+    assert torch.equal(T.exp, R.exp) and torch.equal(T.mant, R.mant)
+
+
 def test_lowered_and_regrouped_operands():
     """Repacked operands (groups of 8 and 64, a precision between chunk
     boundaries) in parts and on the few-output kernel."""
