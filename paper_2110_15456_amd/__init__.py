@@ -351,17 +351,17 @@ def _gemm_out(A, B, out):
 
 def _gemm_with_workspace(A, B, m_a, m_b, C, workspace):
     """bfp_gemm_ws: operands the block-scaled kernel cannot read as stored are
-    repacked into a workspace (torch-allocated unless one is given)."""
+    repacked into a workspace (torch-allocated unless one is given).  A given one
+    is left alone where none is needed: it may be on another device, or another
+    stream's for such products."""
     packed = 1 if isinstance(A, PackedBFPTensor) else 0
     if isinstance(workspace, torch.Tensor):
-        need = gemm_ws_size(A, B, m_a, m_b)
-        ws = workspace
+        need, ws = gemm_ws_size(A, B, m_a, m_b), None
         if need > 0:
             _need_cuda(workspace, "workspace", torch.uint8)
             if workspace.numel() < need:
                 raise ValueError("workspace needs %d bytes" % need)
-        elif not workspace.is_cuda or workspace.dtype != torch.uint8 or not workspace.is_contiguous():
-            ws = None  # none is needed
+            ws = workspace
     else:
         need = _full_ws(A.m, B.m, A.rows, B.rows, A.len, A.g, m_a, m_b, packed)
         ws = torch.empty(need, dtype=torch.uint8, device=A.device) if need else None
@@ -384,8 +384,14 @@ def gemm(A: BFPTensor, B: BFPTensor, m_a: int | None = None, m_b: int | None = N
     workspace: True (default) runs every product on the block-scaled kernel,
     repacking an operand it cannot read as stored (groups of 4, 8, 64; a
     precision between chunk boundaries) into a workspace allocated here
-    (bfp_gemm_ws), or into a given uint8 CUDA tensor; False calls bfp_gemm,
-    which runs such products on its allocation-free general kernel.
+    (bfp_gemm_ws), which also holds the sums of a product whose K is taken in
+    parts.  A given uint8 CUDA tensor of at least gemm_ws_size bytes takes its
+    place; nothing is allocated then.  It is overwritten if that size is not
+    zero (the parts' sums go behind the operands where it holds them, so calls
+    that share it must not overlap), and otherwise left alone, with K in one
+    run.  False calls bfp_gemm, which runs the products that need a workspace
+    on its allocation-free general kernel.  The order in which a product's
+    FP32 terms are added depends on its sizes and on this argument.
     """
     m_a, m_b = _gemm_args(A, B, m_a, m_b)
     C = _gemm_out(A, B, out)

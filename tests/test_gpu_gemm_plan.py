@@ -82,6 +82,20 @@ def test_parts(g, mm, shape):
     assert torch.equal(W, fb.gemm(A, B, workspace=False))
 
 
+def test_given_workspace_is_left_alone():
+    """A tensor given for a product that needs no workspace is not written, however
+    large: programs share one among streams."""
+    M, N, K = 300, 270, 16384
+    for m in (4, 6):
+        announce("given workspace %dx%dx%d m=%d" % (M, N, K, m))
+        A, B, _, _ = make(M, N, K, 16, m, m, 7200)
+        assert fb.gemm_ws_size(A, B) == 0 and full_size(A, B) > 0
+        ws = torch.full((full_size(A, B),), 0xA5, dtype=torch.uint8, device="cuda")
+        C = fb.gemm(A, B, workspace=ws)
+        assert bool((ws == 0xA5).all())
+        assert torch.equal(C, fb.gemm(A, B, workspace=False))
+
+
 @pytest.mark.parametrize("mm", [(4, 4), (6, 4), (2, 8)])
 @pytest.mark.parametrize("shape", [(33, 80, 1040), (300, 272, 16384), (144, 64, 90112)])
 def test_converted_output(mm, shape):
