@@ -2,7 +2,11 @@
 (int8 MFMA) with the oracle.  Group partials must be bit-exact; every FP32
 output must satisfy |C_gpu - C_oracle| <= 1e-6 * sum_G |T_G| (the oracle sums
 in double).  Operands are quantized on both sides from the same FP32 inputs,
-and their quantized bytes are checked bit-exact first."""
+and their quantized bytes are checked bit-exact first.
+
+Without a forced tile the products go through fb.gemm's default route
+(bfp_gemm_ws), which gives the small ones to the few-output kernel;
+test_gpu_gemm_routes.py runs the same shapes on the tiled kernel."""
 from __future__ import annotations
 
 import numpy as np
@@ -128,9 +132,9 @@ def test_tiled_auto_matches_default_tile():
 
 @pytest.mark.parametrize("nslabs", range(1, 10))
 def test_full_slab_counts(nslabs):
-    """K = 128 * nslabs (full slabs: exponents by direct loads, two slabs' per
-    16-byte load, and the slab loop unrolled by four): every slab count mod 4
-    (the loop's tail) for each kernel family, with ragged M and N."""
+    """K = 128 * nslabs, ragged M and N, on the kernel that the default route
+    takes (test_gpu_gemm_routes.py: every tail of the tiled kernel's slab
+    loop)."""
     M, N, K = 260, 136, 128 * nslabs
     xa = synth.draw("normal", (M, K), 700 + nslabs)
     xb = synth.draw("weights", (N, K), 800 + nslabs)

@@ -40,7 +40,8 @@ def full_size(A, B):
     return nb.value
 
 
-# tile edges of 16, 32 and 64 rows, odd column counts, one unit of K to ragged
+# edges of the 16 x 16 tile, which the plan takes for all of these (the larger
+# ones: test_gpu_gemm_routes.py), odd column counts, one unit of K to ragged
 # supersteps (16 units) and more supersteps than waves
 @pytest.mark.parametrize("g", [16, 32])
 @pytest.mark.parametrize("shape", [(1, 40, 32), (17, 33, 288), (31, 161, 1056), (65, 150, 2592), (3, 65, 4640)])
