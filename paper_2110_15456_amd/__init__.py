@@ -429,7 +429,9 @@ def gemm_bfp(A: BFPTensor, B: BFPTensor, c_m: int, m_a: int | None = None, m_b: 
              out: BFPTensor | None = None) -> BFPTensor:
     """C = A . B^T converted to BFP in the GEMM's epilogue: a [A.rows, B.rows]
     BFP tensor with groups of 16 along each row of C at c_m bits, equal to
-    quantize(gemm(A, B), g=16, m=c_m, rounding, seed)."""
+    quantize(gemm(A, B), g=16, m=c_m, rounding, seed), bit for bit.  (Of
+    gemm(A, B, workspace=False) only up to the order in which C's terms are
+    added: that call takes no product in parts nor on the few-output kernel.)"""
     if rounding not in ROUNDING:
         raise ValueError("rounding must be one of %s" % sorted(ROUNDING))
     m_a, m_b = _gemm_args(A, B, m_a, m_b)
