@@ -62,17 +62,8 @@ namespace mx {
 #ifndef FASTBFP_MX_BN
 #define FASTBFP_MX_BN 256
 #endif
-#ifndef FASTBFP_MX_PIPE11
-#define FASTBFP_MX_PIPE11 1
-#endif
 #ifndef FASTBFP_MX_SPREAD
 #define FASTBFP_MX_SPREAD 8  // parts a slab's loads are spread over (explicit pipeline)
-#endif
-#ifndef FASTBFP_MX_X3
-#define FASTBFP_MX_X3 1  // one MFMA for both cross products of two-chunk operands
-#endif
-#ifndef FASTBFP_MX_PIPE2
-#define FASTBFP_MX_PIPE2 1
 #endif
 #ifndef FASTBFP_MX_GM
 #define FASTBFP_MX_GM (CF::BM > CF::BN ? 4 : 8)
@@ -118,12 +109,12 @@ struct Cfg {
   static constexpr int SPARE = OFF_EB + BN * EK;  // EK bytes written by threads without an exponent row
   static constexpr int STAGE = SPARE + 16;
   static constexpr int EXP_ROWS_PER_T = (BM + BN + NT - 1) / NT;
-  // Explicitly software-pipelined fragment reads (one chunk per operand);
-  // otherwise the compiler schedules them.
   // Waves per SIMD the registers have to leave room for: two where a tile's
   // accumulators take at most half of them (two workgroups per CU).
   static constexpr int WAVES = TM * TN * 4 <= 128 && NA == 1 && NB == 1 ? 2 : 1;
-  static constexpr bool PIPE = FASTBFP_MX_PIPE11 && NA == 1 && NB == 1 && G == 16;
+  // One chunk plane per operand, groups of 16: the pipeline through the slab
+  // barriers.
+  static constexpr bool PIPE = NA == 1 && NB == 1 && G == 16;
   static_assert(TM * 16 * WGM == BM && TN * 16 * WGN == BN, "wave tiles cover the tile");
   static_assert((BM + BN) % 64 == 0 && BM % 64 == 0 && BN % 64 == 0,
                 "loads split evenly over the waves; whole waves skip exponent rows past BM + BN");
@@ -339,21 +330,20 @@ __device__ __forceinline__ void load_exps_pair(uint8_t* lds_x, rsrc_t rsrc, uint
   }
 }
 
-// MFMA operands of one K-step from the 16-byte slots read for A (x) and B (y).
-// A lane's block is values 0..15 (half 0) and 16..31 (half 1).  An FP6 slot
-// has its group in half 0 (dwords 0-2; dword 3 is the slot's zero dword and
-// A's upper registers are zero); an FP4 slot has the pair (2 lb, 2 lb + 1) in
-// dwords 0-1 and 2-3, the active group 2 lb + ks in half ks.  The two active
-// groups must meet, and every other product must meet a zero:
+// MFMA operands of one K-step from the 16-byte slots read for A (x) and B (y),
+// at least one of them FP6.  A lane's block is values 0..15 (half 0) and 16..31
+// (half 1).  An FP6 slot has its group in half 0 (dwords 0-2; dword 3 is the
+// slot's zero dword and A's upper registers are zero); an FP4 slot has the pair
+// (2 lb, 2 lb + 1) in dwords 0-1 and 2-3, the active group 2 lb + ks in half ks.
+// The two active groups must meet, and every other product must meet a zero:
 //   FP6 x FP6: A has zeros in half 1, B as read;
-//   FP4 x FP4: A as read, B keeps its active half and zeroes the other;
 //   FP6 x FP4: B's active group moves to half 0 (A's half 1 is zero);
 //   FP4 x FP6: A's active group moves to half 0, B's half 1 is zeroed.
 template <int FA, int FB>
 __device__ __forceinline__ v8i op_a(const u32x4& x, int ks) {
+  static_assert(!FA || !FB, "FP4 on both sides is filled from LDS (fill_a)");
   const v4i& v = reinterpret_cast<const v4i&>(x);
   if constexpr (!FA) return v8i{v[0], v[1], v[2], v[3], 0, 0, 0, 0};
-  else if constexpr (FB) return __builtin_shufflevector(v, v, 0, 1, 2, 3, -1, -1, -1, -1);
   else return ks ? __builtin_shufflevector(v, v, 2, 3, -1, -1, -1, -1, -1, -1)
                  : __builtin_shufflevector(v, v, 0, 1, 2, 3, -1, -1, -1, -1);
 }
@@ -362,18 +352,10 @@ __device__ __forceinline__ v8i op_b(const u32x4& y, int ks) {
   const v4i& v = reinterpret_cast<const v4i&>(y);
   if constexpr (!FB && !FA) return __builtin_shufflevector(v, v, 0, 1, 2, 3, -1, -1, -1, -1);
   else if constexpr (!FB) return v8i{v[0], v[1], v[2], v[3], 0, 0, 0, 0};
-  else if constexpr (!FA)
+  else
     return ks ? __builtin_shufflevector(v, v, 2, 3, -1, -1, -1, -1, -1, -1)
               : __builtin_shufflevector(v, v, 0, 1, 2, 3, -1, -1, -1, -1);
-  else return ks ? v8i{0, 0, v[2], v[3], 0, 0, 0, 0} : v8i{v[0], v[1], 0, 0, 0, 0, 0, 0};
 }
-// The MFMA operand format code of a plane: FP6 E2M3 = 2, FP4 E2M1 = 4 (as a
-// template constant: the intrinsic needs a literal).
-template <int FP4> struct mfma_fmt { static constexpr int value = FP4 ? 4 : 2; };
-
-#ifndef FASTBFP_MX_TIED
-#define FASTBFP_MX_TIED 1
-#endif
 typedef int v6i __attribute__((ext_vector_type(6)));
 typedef int v2i __attribute__((ext_vector_type(2)));
 // acc += the block-scaled product of one K-step (A format FA, B format FB,
@@ -389,52 +371,28 @@ typedef int v2i __attribute__((ext_vector_type(2)));
 // wait), and mma_drain() covers the reads after it.  The statement is not
 // volatile: a volatile one would also keep the scheduler from moving fragment
 // reads across it.
-// SA / SB: which byte of sa / sb is the block scale (the instruction's
-// op_sel bits for its second / first source): 0 for the low byte, 1 for the
-// next, so that one 16-bit exponent read serves both K-steps of a slab.
 #define FASTBFP_MFMA_ASM(SEL, CB, BG) \
   "s_nop 1\n\tv_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 " SEL " cbsz:" #CB " blgp:" #BG
-#define FASTBFP_MFMA_SEL(CB, BG, BOP, AOP)                                                                      \
-  {                                                                                                            \
-    if constexpr (SA == 0 && SB == 0)                                                                          \
-      asm(FASTBFP_MFMA_ASM("op_sel_hi:[0,0,0]", CB, BG) : "+a"(acc) : "v"(BOP), "v"(AOP), "v"(sb), "v"(sa));    \
-    else if constexpr (SA == 0)                                                                                \
-      asm(FASTBFP_MFMA_ASM("op_sel:[1,0,0] op_sel_hi:[0,0,0]", CB, BG)                                         \
-          : "+a"(acc) : "v"(BOP), "v"(AOP), "v"(sb), "v"(sa));                                                 \
-    else if constexpr (SB == 0)                                                                                \
-      asm(FASTBFP_MFMA_ASM("op_sel:[0,1,0] op_sel_hi:[0,0,0]", CB, BG)                                         \
-          : "+a"(acc) : "v"(BOP), "v"(AOP), "v"(sb), "v"(sa));                                                 \
-    else                                                                                                       \
-      asm(FASTBFP_MFMA_ASM("op_sel:[1,1,0] op_sel_hi:[0,0,0]", CB, BG)                                         \
-          : "+a"(acc) : "v"(BOP), "v"(AOP), "v"(sb), "v"(sa));                                                 \
-  }
-template <int FA, int FB, int SA = 0, int SB = 0>
+#define FASTBFP_MFMA(CB, BG, BOP, AOP) \
+  asm(FASTBFP_MFMA_ASM("op_sel_hi:[0,0,0]", CB, BG) : "+a"(acc) : "v"(BOP), "v"(AOP), "v"(sb), "v"(sa))
+template <int FA, int FB>
 __device__ __forceinline__ void mma(v4f& acc, const v8i& a, const v8i& b, int sa, int sb) {
-  static_assert(SA == 0 || SA == 1, "scale byte 0 or 1");
-  static_assert(SB == 0 || SB == 1, "scale byte 0 or 1");
   // B's fragment is the instruction's first operand and A's the second, so
   // the result is the tile of C transposed: a lane's four accumulators are
   // four consecutive columns of one row of C (see the epilogue).
-#if FASTBFP_MX_TIED
   const v4i a4 = __builtin_shufflevector(a, a, 0, 1, 2, 3);
   const v4i b4 = __builtin_shufflevector(b, b, 0, 1, 2, 3);
   const v6i a6 = __builtin_shufflevector(a, a, 0, 1, 2, 3, 4, 5);
   const v6i b6 = __builtin_shufflevector(b, b, 0, 1, 2, 3, 4, 5);
-  if constexpr (FA && FB)
-    FASTBFP_MFMA_SEL(4, 4, b4, a4)
-  else if constexpr (FA)
-    FASTBFP_MFMA_SEL(2, 4, b6, a4)
-  else if constexpr (FB)
-    FASTBFP_MFMA_SEL(4, 2, b4, a6)
-  else
-    FASTBFP_MFMA_SEL(2, 2, b6, a6)
-#else
-  acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b, a, acc, mfma_fmt<FB>::value, mfma_fmt<FA>::value, SB, sb,
-                                                         SA, sa);
-#endif
+  if constexpr (FA && FB) FASTBFP_MFMA(4, 4, b4, a4);
+  else if constexpr (FA) FASTBFP_MFMA(2, 4, b6, a4);
+  else if constexpr (FB) FASTBFP_MFMA(4, 2, b4, a6);
+  else FASTBFP_MFMA(2, 2, b6, a6);
 }
 // The same on operands held in the registers the instruction reads (six for
-// FP6, four for FP4).
+// FP6, four for FP4).  KS: which byte of sa and sb is the block scale (the
+// instruction's op_sel bits), so that one 16-bit exponent read serves both
+// K-steps of a slab.
 template <int F> struct opnd { typedef v6i type; };
 template <> struct opnd<1> { typedef v4i type; };
 #define FASTBFP_MFMA_ASM2(SEL, CB, BG) \
@@ -465,7 +423,7 @@ __device__ __forceinline__ void mma_held(v4f& acc, const A& a, const B& b, int s
 }
 #undef FASTBFP_MFMA_SEL2
 #undef FASTBFP_MFMA_ASM2
-#undef FASTBFP_MFMA_SEL
+#undef FASTBFP_MFMA
 #undef FASTBFP_MFMA_ASM
 // Wait states between the last MFMA and any other read of its accumulators
 // (a 16x16x128 block-scaled MFMA needs at most 19).  Every accumulator then
@@ -475,13 +433,11 @@ __device__ __forceinline__ void mma_held(v4f& acc, const A& a, const B& b, int s
 // barrier orders -- depends on it.
 template <int TM, int TN>
 __device__ __forceinline__ void mma_drain(v4f (&acc)[TM][TN]) {
-#if FASTBFP_MX_TIED
   asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
-#endif
 }
 
 // Where the epilogue puts C: FP32 rows (QNCH = 0), or BFP with groups of 16
@@ -511,11 +467,12 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
   // the load instructions of per-slab dword loads.  The stages then hold only mantissas (and the converted output's
   // strips).  Otherwise each stage holds its slab's exponents.
   constexpr bool XP = EXP_FULL && CF::G == 16;
-  constexpr bool X3 = FASTBFP_MX_X3 && NA == 2 && NB == 2 && CF::G == 16 && !CF::PIPE && !FA && !FB;
+  // both operands split at 4 bits: one MFMA for both cross products
+  constexpr bool X3 = NA == 2 && NB == 2 && CF::G == 16 && !FA && !FB;
   // an operand split at 2 bits fills whole MFMA blocks (groups of 16)
   constexpr bool COMB = CF::G == 16 && ((NA == 2 && FA) || (NB == 2 && FB));
-  // explicit pipeline of the two-chunk loop (operands split at 4 bits)
-  constexpr bool PIPE2 = FASTBFP_MX_PIPE2 && (NA == 2 || NB == 2) && CF::G == 16 && !X3 && !COMB;
+  // explicit pipeline of the two-chunk loop (one operand split at 4 bits)
+  constexpr bool PIPE2 = (NA == 2 || NB == 2) && CF::G == 16 && !X3 && !COMB;
   constexpr int NTHR = CF::NT;
   constexpr int STRIP_BYTES = QNCH ? CF::NW * 16 * (CF::WN + 4) * 4 : 0;
   constexpr int SB = XP ? (CF::OFF_EA > STRIP_BYTES ? CF::OFF_EA : STRIP_BYTES) : CF::STAGE;
@@ -533,7 +490,7 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
   int tm, tn;
   // K in parts (part_slabs > 0): this workgroup sums slabs [slab0, slab0 +
   // part_slabs) into its part's own FP32 matrix, part_stride values after the
-  // previous one (launch_split_sum adds them up).
+  // previous one (launch_parts_sum adds them up).
   int slab0 = 0;
   if (QNCH == 0 && part_slabs > 0) {
     const int part = split_tile_of<FASTBFP_MX_GM>(blockIdx.x, gridDim.x, tiles_m, tiles_n, tm, tn);
@@ -745,7 +702,7 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
       return fp4 ? plane_off + (r + 16 * t) * 64 + ((lb ^ swz4) * 16)
                  : plane_off + (r + 16 * t) * 128 + (((2 * lb + ks) ^ swz6) * 16);
     };
-    // An operand's registers from its LDS slot (the rules of op_a / op_b): FP6,
+    // An operand's registers from its LDS slot: FP6,
     // the slot's 16 bytes below two zero registers; FP4 against FP4, A's pair as
     // read and B's active group in its half of a zeroed block; FP4 against FP6,
     // the active group in half 0 (the other operand's half 1 is zero).
@@ -1179,17 +1136,11 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
     asm volatile("" ::: "memory");
     const bool more = s + 1 < nslabs;
     const int nslab = more ? s + 1 : s;
-    // With an FP6 operand the loads go out in NPART parts between the blocks
-    // of MFMAs, so that the wave keeps issuing MFMAs while the load path works
-    // through them (FP6 x FP6: 10-14% faster, two
-    // chunk planes 1-12%).  FP4 x FP4 slabs have half the load instructions,
-    // and there issuing them all at once, here, is faster (their latency, not
-    // their issue, is what shows).
-    // (The same holds for groups of 32, whose slabs are one K-step: there
-    // spreading was 1-4% slower.)
-    constexpr int NPART = ((NA == 1 && NB == 1 && FA && FB) || CF::G == 32)
-                              ? 1
-                              : (NLOAD < FASTBFP_MX_SPREAD ? NLOAD : FASTBFP_MX_SPREAD);
+    // The loads go out in NPART parts between the blocks of MFMAs, so that the
+    // wave keeps issuing MFMAs while the load path works through them (two
+    // chunk planes 1-12% faster).  With groups of 32, whose slabs are one
+    // K-step, all at once, here: there spreading was 1-4% slower.
+    constexpr int NPART = CF::G == 32 ? 1 : (NLOAD < FASTBFP_MX_SPREAD ? NLOAD : FASTBFP_MX_SPREAD);
     // The parts go after MFMA blocks spread over the first half of the slab's
     // nblk blocks (part k after block k * (nblk / 2) / NPART), each fenced so
     // that the compiler keeps it there.
@@ -1319,7 +1270,8 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
         issue_after(blk, NBLK);
         __builtin_amdgcn_sched_barrier(0);
       });
-    } else if constexpr (X3) {
+    } else {
+      static_assert(X3, "the products of two-chunk operands");
       // Both operands in two chunk planes: the cross products (A's upper
       // chunk with B's lower, A's lower with B's upper) carry the same weight,
       // one chunk of significance, and with groups of 16 each fills only half
@@ -1356,40 +1308,6 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
           }
           issue_after(ks * TM + i, 2 * TM);
         }
-      }
-    } else {
-      // Compiler-scheduled: per K-step, the B fragments of every chunk plane,
-      // then each A fragment (read once, its exponent byte once) against
-      // them.  A block is one A fragment's MFMAs; the load parts go between
-      // blocks.
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        u32x4 y[NB][TN];
-        int eb[NB][TN];
-        static_for<NB>([&](auto cbc) {
-          constexpr int cb = decltype(cbc)::value, fb = mx::b_fp4<CF>(cb);
-#pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            y[cb][j] = rd(slot_addr(mx::b_plane<CF>(cb), fb, b_r, j, ks));
-            // +4 per chunk of significance
-            eb[cb][j] = (int)xcur[eb_lane + j * 16 * ER + ks] + 4 * (NB - 1 - cb);
-          }
-        });
-        static_for<NA>([&](auto cac) {
-          constexpr int ca = decltype(cac)::value, fa = mx::a_fp4<CF>(ca);
-#pragma unroll
-          for (int i = 0; i < TM; ++i) {
-            const u32x4 x = rd(slot_addr(mx::a_plane<CF>(ca), fa, a_r, i, ks));
-            const int ea = (int)xcur[ea_lane + i * 16 * ER + ks] + 4 * (NA - 1 - ca);
-            static_for<NB>([&](auto cbc) {
-              constexpr int cb = decltype(cbc)::value, fb = mx::b_fp4<CF>(cb);
-              const v8i av = op_a<fa, fb>(x, ks);
-#pragma unroll
-              for (int j = 0; j < TN; ++j) mma<fa, fb>(acc[i][j], av, op_b<fa, fb>(y[cb][j], ks), ea, eb[cb][j]);
-            });
-            issue_after((ks * NA + ca) * TM + i, 2 * NA * TM);
-          }
-        });
       }
     }
     __builtin_amdgcn_sched_barrier(0);
