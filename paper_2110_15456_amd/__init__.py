@@ -349,6 +349,18 @@ def _gemm_out(A, B, out):
     return C
 
 
+def _workspace(need, least, device):
+    """`need` bytes; where the card has no room for them the `least()` bytes that
+    the product cannot do without (None for none), with K in one run then."""
+    try:
+        return torch.empty(need, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        less = least()
+        if less == need:
+            raise
+    return torch.empty(less, dtype=torch.uint8, device=device) if less else None
+
+
 def _gemm_with_workspace(A, B, m_a, m_b, C, workspace):
     """bfp_gemm_ws: operands the block-scaled kernel cannot read as stored are
     repacked into a workspace (torch-allocated unless one is given).  A given one
@@ -364,7 +376,7 @@ def _gemm_with_workspace(A, B, m_a, m_b, C, workspace):
             ws = workspace
     else:
         need = _full_ws(A.m, B.m, A.rows, B.rows, A.len, A.g, m_a, m_b, packed)
-        ws = torch.empty(need, dtype=torch.uint8, device=A.device) if need else None
+        ws = _workspace(need, lambda: gemm_ws_size(A, B, m_a, m_b), A.device) if need else None
     check(load().bfp_gemm_ws(A.mant.data_ptr(), A.exp.data_ptr(), A.m, B.mant.data_ptr(), B.exp.data_ptr(), B.m, A.rows,
                              B.rows, A.len, A.g, m_a, m_b, packed, C.data_ptr(), C.stride(0),
                              ws.data_ptr() if ws is not None else None,
@@ -385,7 +397,7 @@ def gemm(A: BFPTensor, B: BFPTensor, m_a: int | None = None, m_b: int | None = N
     repacking an operand it cannot read as stored (groups of 4, 8, 64; a
     precision between chunk boundaries) into a workspace allocated here
     (bfp_gemm_ws), which also holds the sums of a product whose K is taken in
-    parts.  A given uint8 CUDA tensor of at least gemm_ws_size bytes takes its
+    parts (in one run where the card has no room for them).  A given uint8 CUDA tensor of at least gemm_ws_size bytes takes its
     place; nothing is allocated then.  It is overwritten if that size is not
     zero (the parts' sums go behind the operands where it holds them, so calls
     that share it must not overlap), and otherwise left alone, with K in one
@@ -443,13 +455,13 @@ def gemm_bfp(A: BFPTensor, B: BFPTensor, c_m: int, m_a: int | None = None, m_b: 
         _need_cuda(status, "status")
         st_ptr = status.data_ptr()
     need = _bfp_ws(A.m, B.m, A.rows, B.rows, A.len, A.g, m_a, m_b)
-    ws = torch.empty(need, dtype=torch.uint8, device=A.device) if need else None
+    ws = _workspace(need, lambda: 0, A.device) if need else None
     check(load().bfp_gemm_bfp_ws(A.mant.data_ptr(), A.exp.data_ptr(), A.m,
                                  B.mant.data_ptr(), B.exp.data_ptr(), B.m, A.rows,
                                  B.rows, A.len, A.g, m_a, m_b, c_m, ROUNDING[rounding],
                                  seed & 0xFFFFFFFFFFFFFFFF, t.mant.data_ptr(),
                                  t.exp.data_ptr(), st_ptr,
-                                 ws.data_ptr() if ws is not None else None, need,
+                                 ws.data_ptr() if ws is not None else None, ws.numel() if ws is not None else 0,
                                  _stream(A.device)), "bfp_gemm_bfp")
     return t
 

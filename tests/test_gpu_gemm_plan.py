@@ -97,6 +97,39 @@ def test_given_workspace_is_left_alone():
         assert torch.equal(C, fb.gemm(A, B, workspace=False))
 
 
+def test_without_memory_for_the_parts():
+    """Products whose parts' sums find no room on the card run in one run over K."""
+    M, N, K = 1024, 4096, 16384
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    A, B = (fb.quantize(torch.randn((r, K), device="cuda", generator=gen), m=4) for r in (M, N))
+    P, Q = (fb.quantize(torch.randn((r, K), device="cuda", generator=gen), g=8, m=4) for r in (M, N // 4))
+    assert full_size(A, B) > 60 << 20 and full_size(P, Q) - fb.gemm_ws_size(P, Q) > 15 << 20
+    want = fb.gemm(A, B, workspace=False)
+    want_rep = fb.gemm(P, Q, workspace=torch.empty(fb.gemm_ws_size(P, Q), dtype=torch.uint8, device="cuda"))
+    R = fb.quantize(want, m=4)
+    C, D, T = torch.empty_like(want), torch.empty_like(want_rep), fb.BFPTensor.empty(M, N, 16, 4, "cuda")
+    room = torch.empty(fb.gemm_ws_size(P, Q), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = []
+    try:
+        announce("no memory for parts %dx%dx%d" % (M, N, K))
+        torch.cuda.set_per_process_memory_fraction(
+            torch.cuda.memory_reserved() / torch.cuda.get_device_properties(0).total_memory)
+        for mib in (64, 16, 4):  # what the allocator still holds free
+            with pytest.raises(torch.OutOfMemoryError):
+                while len(held) < 1000:
+                    held.append(torch.empty(mib << 20, dtype=torch.uint8, device="cuda"))
+        fb.gemm(A, B, out=C)
+        fb.gemm_bfp(A, B, 4, out=T)
+        del room
+        fb.gemm(P, Q, out=D)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.equal(C, want) and torch.equal(D, want_rep)
+    assert torch.equal(T.mant, R.mant) and torch.equal(T.exp, R.exp)
+
+
 @pytest.mark.parametrize("mm", [(4, 4), (6, 4), (2, 8)])
 @pytest.mark.parametrize("shape", [(33, 80, 1040), (300, 272, 16384), (144, 64, 90112)])
 def test_converted_output(mm, shape):
