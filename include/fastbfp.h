@@ -252,8 +252,9 @@ int bfp_repack(const uint8_t* mant, const uint8_t* exp, int64_t rows, int64_t le
  * MFMA kernel: an operand the kernel cannot read as stored -- a group size of
  * 4, 8 or 64, a precision that is not a chunk boundary, or packed storage
  * (packed = 1: both operands in the packed storage, g = 16) -- is first
- * re-encoded into the workspace by bfp_repack at (m_a, m_b), and the kernel
- * then runs on K_out = len_out with groups of g_out.  Products bfp_gemm
+ * re-encoded into the workspace as bfp_repack does at (m_a, m_b) (of groups of
+ * 64 at a chunk boundary only the exponents, the planes are read in place), and
+ * the kernel then runs on K_out = len_out with groups of g_out.  Products bfp_gemm
  * already runs on that kernel need no workspace.  bfp_gemm itself keeps
  * running the other cases on its general kernel, allocation- and
  * workspace-free, at a far lower rate.
@@ -307,7 +308,7 @@ int bfp_gemm_ws_route(int a_m_bits, int b_m_bits, int64_t M, int64_t N, int64_t 
  * A product that bfp_gemm runs on its general kernel takes only tile = -1
  * (BFP_E_UNSUPPORTED otherwise).
  * For one-chunk, g = 16 products bfp_gemm picks 128 x 64 when N <= 64;
- * 256 x 128 when A's plane holds FP4 codes (A stored with m = 1, 2, 5 or 6);
+ * 256 x 128 when A's plane holds FP4 codes (A stored with m = 1 or 2);
  * otherwise 256 x 256, or 128 x 128 when N <= 128; and it steps down to a
  * smaller tile while fewer than 192 tiles would leave CUs idle.  Every tile
  * computes the same products, per-group scales and per-output accumulation

@@ -61,19 +61,25 @@ FASTBFP_DIRECT_ALL(FASTBFP_DIRECT_DECLARE, 2, 2, 32)
 
 // Tile of the one-chunk, groups-of-16, FP32-output GEMM (0..4: 256x256,
 // 256x128, 256x64, 128x64, 128x128), from measurements on MI355X over the
-// transformer, FFN-step and ResNet-18 im2col shapes:
-//  * N <= 64: 128x64 (a wider tile is mostly padding; 256x64 was never the
-//    fastest);
-//  * A in FP4 codes: 256x128 (5-11% faster than 256x256 on the transformer
-//    shapes: its two LDS stages take 60-76 KB, so two workgroups share a CU);
+// transformer, FFN-step and ResNet-18 im2col shapes (every tile forced, us):
+//  * N <= 64: 128x64, a wider tile is mostly padding (802816 x 64 x 576 (2,2) 91
+//    against 109-292 on the others, (4,4) 155 against 181-325; only (4,2) has
+//    256x64 ahead, 144 against 148);
+//  * A in FP4 codes: 256x128, whose two LDS stages take 60-76 KB, so that two
+//    workgroups share a CU: 1-10% faster than 256x256 on 8192 x 4096, 12288 and
+//    16384 x 4096 (457 against 506 on the last, (2,2)), 1-3% slower on 8192 x 4096
+//    x 16384;
 //  * A in FP6 codes: 256x256 (a 256x128 tile still takes 92-108 KB of LDS, one
-//    workgroup per CU, and ran 30-40% slower; 128x128, two per CU, 15-35%
+//    workgroup per CU, and is 27-45% slower; 128x128, two per CU, 16-48%
 //    slower), but 128x128 for N <= 128 or when 256x256 tiles are too few;
 //  * too few: fewer than 192 tiles leave over a quarter of the 256 CUs idle;
 //    then the next smaller tile, down to 128x64.
 // With C converted to BFP in the epilogue (converted), A in FP4 codes gets
-// the FP6 rule: there the 256x128 tile was the slower one (ffn_up (2,2) to
-// m = 2: 0.71 ms against 0.60-0.63 ms on 256x256).
+// the FP6 rule.  That line was drawn when a slab began with a barrier and the
+// reads waited for (8192 x 16384 x 4096 (2,2) to m = 2: 600-630 us on 256x256, 710
+// on 256x128).  With the pipeline through the slab barriers it is 510 against
+// 440-475, 50176 x 256 x 2304 47 against 39, 8192 x 4096 x 16384 392 against 383,
+// and 12544 x 512 x 4608, which has the 128x128 tile here, 41 against 45.
 static int gemm_mx11_tile(int64_t M, int64_t N, int fa, bool converted) {
   constexpr int64_t MIN_TILES = 192;
   auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
@@ -197,15 +203,16 @@ GemmPlan gemm_plan_whole(int a_m, int na, int nb, int64_t M, int64_t N, int g) {
 // and the cheapest is taken: every tile with K in as many parts as fill one or
 // more workgroups per CU, and the few-output kernel.  Prices in us, from sweeps
 // of every tile x parts and of the few-output kernel's tiles over weight
-// gradients, few-token and small products on MI355X (measured, best of each):
-//   576 x 64 x 802816 (2,2)     3905 -> 84  (128x64 in 96 parts)
-//   2304 x 256 x 50176 (4,4)     263 -> 55  (256x256 in 28 parts)
-//   1024 x 4096 x 16384 (4,4)    126 -> 93  (256x256 in 4 parts)
-//   1024 x 1024 x 8192 (6,6)     134 -> 37  (256x128 in 8 parts)
-//   16 x 16384 x 4096 (4,4)       23 -> 17  (few-output, 32 x 32)
-//   1 x 4096 x 4096 (4,4)         17 -> 4.9 (few-output, 16 x 16)
-//   256 x 256 x 256 (4,4)        4.4 -> 2.6 (few-output, 16 x 16)
-//   2048 x 1024 x 4096 (4,4)    25.0, any split 30 or more: whole
+// gradients, few-token and small products on MI355X.  What the plan takes, and
+// its time against bfp_gemm's (graph replays of ten calls):
+//   576 x 64 x 802816 (2,2)     4204 -> 89  (128x64 in 102 parts)
+//   2304 x 256 x 50176 (4,4)     285 -> 54  (256x128 in 14 parts)
+//   1024 x 4096 x 16384 (4,4)    136 -> 88  (256x256 in 4 parts)
+//   1024 x 1024 x 8192 (6,6)     134 -> 39  (256x128 in 8 parts)
+//   16 x 16384 x 4096 (4,4)       25 -> 17  (few-output, 32 x 32)
+//   1 x 4096 x 4096 (4,4)         17 -> 5.1 (few-output, 16 x 16)
+//   256 x 256 x 256 (4,4)        5.2 -> 3.0 (few-output, 16 x 16)
+//   2048 x 1024 x 4096 (4,4)      25 -> 24  (whole, 128x64; any split 30 or more)
 GemmPlan gemm_plan(int a_m, int na, int b_m, int nb, int64_t M, int64_t N, int64_t K, int g) {
   const int fa = fmt_flag(a_m, na), fb = fmt_flag(b_m, nb);
   const bool one = na == 1 && nb == 1 && g == 16;
@@ -216,6 +223,10 @@ GemmPlan gemm_plan(int a_m, int na, int b_m, int nb, int64_t M, int64_t N, int64
 
   // Tiles: rows, columns, and the time of one slab with 1 and with 2 workgroups
   // on a CU (0: they do not fit), for FP6 and for FP4 codes on both sides.
+  // (Measured before the kernel's pipeline ran through the slab barriers.  With it,
+  // on a full card, from K = 16384 and 49152: FP6 256x256 2.08, 256x128 1.25,
+  // 128x128 1.01 and 1.34, 128x64 0.81 and 0.95; FP4 1.43, 1.02 and 1.50, 0.78
+  // and 0.96, 0.58 and 0.73.)
   struct Tile {
     int id, bm, bn;
     double us[2][2];
