@@ -509,7 +509,8 @@ int bfp_gemm_ws(const uint8_t* a_mant, const uint8_t* a_exp, int a_m_bits, const
   int a_m = a_m_bits, b_m = b_m_bits;
   // (with K = 0 nothing is repacked or read: the kernel writes zeros)
   // (groups of 64 at the stored width or without the low chunk plane: the
-  // planes are those of groups of 32, only the exponents are doubled)
+  // planes are those of groups of 32, only the exponents are doubled; the room
+  // that bfp_gemm_ws_size counts for such an operand's mantissas is not used)
   const bool twice = !packed && g == 64;
   const bool twice_a = twice && planes_used(a_m_bits, m_a) != 0, twice_b = twice && planes_used(b_m_bits, m_b) != 0;
   if (p.rep_a && twice_a) {
