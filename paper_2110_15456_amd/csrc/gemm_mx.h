@@ -1373,7 +1373,8 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
           }
         }
       };
-      if (part_slabs > 0) store(ic<0>{});
+      const bool lines = (ldc & 31) == 0 && (reinterpret_cast<uintptr_t>(C) & 127) == 0;
+      if (part_slabs > 0 || !lines) store(ic<0>{});
       else store(ic<1>{});
       return;
     }
