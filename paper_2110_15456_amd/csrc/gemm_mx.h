@@ -39,8 +39,8 @@
 // load instruction still reads whole runs of consecutive rows.  With full
 // slabs of groups of 16, the exponents of two slabs come in one 16-byte load
 // per row into a buffer of their own.  Slabs are double buffered in two LDS
-// objects.  The one-chunk kernels and those with an operand split at 2 bits
-// publish slab s+1 a few blocks of MFMAs before slab s ends and read its first
+// objects.  The one-chunk kernels on tiles of 256 rows and 128 columns or more and
+// those with an operand split at 2 bits publish slab s+1 a few blocks of MFMAs before slab s ends and read its first
 // fragments while slab s's last blocks run, so that the matrix cores do not
 // stand still at the barrier; the others issue the loads of slab s+1 right
 // after the barrier that publishes slab s.  Every load
@@ -113,8 +113,9 @@ struct Cfg {
   // accumulators take at most half of them (two workgroups per CU).
   static constexpr int WAVES = TM * TN * 4 <= 128 && NA == 1 && NB == 1 ? 2 : 1;
   // One chunk plane per operand, groups of 16: the pipeline through the slab
-  // barriers.
-  static constexpr bool PIPE = NA == 1 && NB == 1 && G == 16;
+  // barriers, or (LOCAL) one within the slab.
+  static constexpr bool PIPE11 = NA == 1 && NB == 1 && G == 16;
+  static constexpr bool PIPE = PIPE11 && TM * TN >= 32, LOCAL = PIPE11 && !PIPE;
   static_assert(TM * 16 * WGM == BM && TN * 16 * WGN == BN, "wave tiles cover the tile");
   static_assert((BM + BN) % 64 == 0 && BM % 64 == 0 && BN % 64 == 0,
                 "loads split evenly over the waves; whole waves skip exponent rows past BM + BN");
@@ -330,20 +331,21 @@ __device__ __forceinline__ void load_exps_pair(uint8_t* lds_x, rsrc_t rsrc, uint
   }
 }
 
-// MFMA operands of one K-step from the 16-byte slots read for A (x) and B (y),
-// at least one of them FP6.  A lane's block is values 0..15 (half 0) and 16..31
-// (half 1).  An FP6 slot has its group in half 0 (dwords 0-2; dword 3 is the
-// slot's zero dword and A's upper registers are zero); an FP4 slot has the pair
-// (2 lb, 2 lb + 1) in dwords 0-1 and 2-3, the active group 2 lb + ks in half ks.
-// The two active groups must meet, and every other product must meet a zero:
+// MFMA operands of one K-step from the 16-byte slots read for A (x) and B (y).
+// A lane's block is values 0..15 (half 0) and 16..31 (half 1).  An FP6 slot
+// has its group in half 0 (dwords 0-2; dword 3 is the slot's zero dword and
+// A's upper registers are zero); an FP4 slot has the pair (2 lb, 2 lb + 1) in
+// dwords 0-1 and 2-3, the active group 2 lb + ks in half ks.  The two active
+// groups must meet, and every other product must meet a zero:
 //   FP6 x FP6: A has zeros in half 1, B as read;
+//   FP4 x FP4: A as read, B keeps its active half and zeroes the other;
 //   FP6 x FP4: B's active group moves to half 0 (A's half 1 is zero);
 //   FP4 x FP6: A's active group moves to half 0, B's half 1 is zeroed.
 template <int FA, int FB>
 __device__ __forceinline__ v8i op_a(const u32x4& x, int ks) {
-  static_assert(!FA || !FB, "FP4 on both sides is filled from LDS (fill_a)");
   const v4i& v = reinterpret_cast<const v4i&>(x);
   if constexpr (!FA) return v8i{v[0], v[1], v[2], v[3], 0, 0, 0, 0};
+  else if constexpr (FB) return __builtin_shufflevector(v, v, 0, 1, 2, 3, -1, -1, -1, -1);
   else return ks ? __builtin_shufflevector(v, v, 2, 3, -1, -1, -1, -1, -1, -1)
                  : __builtin_shufflevector(v, v, 0, 1, 2, 3, -1, -1, -1, -1);
 }
@@ -352,9 +354,10 @@ __device__ __forceinline__ v8i op_b(const u32x4& y, int ks) {
   const v4i& v = reinterpret_cast<const v4i&>(y);
   if constexpr (!FB && !FA) return __builtin_shufflevector(v, v, 0, 1, 2, 3, -1, -1, -1, -1);
   else if constexpr (!FB) return v8i{v[0], v[1], v[2], v[3], 0, 0, 0, 0};
-  else
+  else if constexpr (!FA)
     return ks ? __builtin_shufflevector(v, v, 2, 3, -1, -1, -1, -1, -1, -1)
               : __builtin_shufflevector(v, v, 0, 1, 2, 3, -1, -1, -1, -1);
+  else return ks ? v8i{0, 0, v[2], v[3], 0, 0, 0, 0} : v8i{v[0], v[1], 0, 0, 0, 0, 0, 0};
 }
 typedef int v6i __attribute__((ext_vector_type(6)));
 typedef int v2i __attribute__((ext_vector_type(2)));
@@ -370,12 +373,20 @@ typedef int v2i __attribute__((ext_vector_type(2)));
 // inside the loop (back-to-back accumulation into the same registers needs no
 // wait), and mma_drain() covers the reads after it.  The statement is not
 // volatile: a volatile one would also keep the scheduler from moving fragment
-// reads across it.
+// reads across it.  KS: which byte of sa and sb is the block scale (the
+// instruction's op_sel bits), so that one 16-bit exponent read serves both
+// K-steps of a slab.
 #define FASTBFP_MFMA_ASM(SEL, CB, BG) \
   "s_nop 1\n\tv_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 " SEL " cbsz:" #CB " blgp:" #BG
-#define FASTBFP_MFMA(CB, BG, BOP, AOP) \
-  asm(FASTBFP_MFMA_ASM("op_sel_hi:[0,0,0]", CB, BG) : "+a"(acc) : "v"(BOP), "v"(AOP), "v"(sb), "v"(sa))
-template <int FA, int FB>
+#define FASTBFP_MFMA(CB, BG, BOP, AOP)                                                                          \
+  {                                                                                                            \
+    if constexpr (KS == 0)                                                                                     \
+      asm(FASTBFP_MFMA_ASM("op_sel_hi:[0,0,0]", CB, BG) : "+a"(acc) : "v"(BOP), "v"(AOP), "v"(sb), "v"(sa));    \
+    else                                                                                                       \
+      asm(FASTBFP_MFMA_ASM("op_sel:[1,1,0] op_sel_hi:[0,0,0]", CB, BG)                                         \
+          : "+a"(acc) : "v"(BOP), "v"(AOP), "v"(sb), "v"(sa));                                                 \
+  }
+template <int FA, int FB, int KS = 0>
 __device__ __forceinline__ void mma(v4f& acc, const v8i& a, const v8i& b, int sa, int sb) {
   // B's fragment is the instruction's first operand and A's the second, so
   // the result is the tile of C transposed: a lane's four accumulators are
@@ -384,15 +395,13 @@ __device__ __forceinline__ void mma(v4f& acc, const v8i& a, const v8i& b, int sa
   const v4i b4 = __builtin_shufflevector(b, b, 0, 1, 2, 3);
   const v6i a6 = __builtin_shufflevector(a, a, 0, 1, 2, 3, 4, 5);
   const v6i b6 = __builtin_shufflevector(b, b, 0, 1, 2, 3, 4, 5);
-  if constexpr (FA && FB) FASTBFP_MFMA(4, 4, b4, a4);
-  else if constexpr (FA) FASTBFP_MFMA(2, 4, b6, a4);
-  else if constexpr (FB) FASTBFP_MFMA(4, 2, b4, a6);
-  else FASTBFP_MFMA(2, 2, b6, a6);
+  if constexpr (FA && FB) FASTBFP_MFMA(4, 4, b4, a4)
+  else if constexpr (FA) FASTBFP_MFMA(2, 4, b6, a4)
+  else if constexpr (FB) FASTBFP_MFMA(4, 2, b4, a6)
+  else FASTBFP_MFMA(2, 2, b6, a6)
 }
 // The same on operands held in the registers the instruction reads (six for
-// FP6, four for FP4).  KS: which byte of sa and sb is the block scale (the
-// instruction's op_sel bits), so that one 16-bit exponent read serves both
-// K-steps of a slab.
+// FP6, four for FP4).
 template <int F> struct opnd { typedef v6i type; };
 template <> struct opnd<1> { typedef v4i type; };
 #define FASTBFP_MFMA_ASM2(SEL, CB, BG) \
@@ -702,7 +711,7 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
       return fp4 ? plane_off + (r + 16 * t) * 64 + ((lb ^ swz4) * 16)
                  : plane_off + (r + 16 * t) * 128 + (((2 * lb + ks) ^ swz6) * 16);
     };
-    // An operand's registers from its LDS slot: FP6,
+    // An operand's registers from its LDS slot (the rules of op_a / op_b): FP6,
     // the slot's 16 bytes below two zero registers; FP4 against FP4, A's pair as
     // read and B's active group in its half of a zeroed block; FP4 against FP6,
     // the active group in half 0 (the other operand's half 1 is zero).
@@ -1137,10 +1146,14 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
     const bool more = s + 1 < nslabs;
     const int nslab = more ? s + 1 : s;
     // The loads go out in NPART parts between the blocks of MFMAs, so that the
-    // wave keeps issuing MFMAs while the load path works through them (two
-    // chunk planes 1-12% faster).  With groups of 32, whose slabs are one
-    // K-step, all at once, here: there spreading was 1-4% slower.
-    constexpr int NPART = CF::G == 32 ? 1 : (NLOAD < FASTBFP_MX_SPREAD ? NLOAD : FASTBFP_MX_SPREAD);
+    // wave keeps issuing MFMAs while the load path works through them (FP6 x FP6
+    // 10-14%, two chunk planes 1-12% faster).  FP4 x FP4 slabs have half the load
+    // instructions, and there issuing them all at once, here, is faster (their
+    // latency, not their issue, is what shows).  With groups of 32, whose slabs
+    // are one K-step, spreading was 1-4% slower.
+    constexpr int NPART = ((NA == 1 && NB == 1 && FA && FB) || CF::G == 32)
+                              ? 1
+                              : (NLOAD < FASTBFP_MX_SPREAD ? NLOAD : FASTBFP_MX_SPREAD);
     // The parts go after MFMA blocks spread over the first half of the slab's
     // nblk blocks (part k after block k * (nblk / 2) / NPART), each fenced so
     // that the compiler keeps it there.
@@ -1193,7 +1206,58 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
       const u32x4 y = rd(slot_addr(plane_off, 0, r, t, 1));
       return v8i{(int)x[0], (int)x[1], (int)x[2], (int)y[0], (int)y[1], (int)y[2], 0, 0};
     };
-    if constexpr (CF::G == 32) {
+    if constexpr (CF::LOCAL) {
+      // One chunk plane per operand on the small tiles, whose registers leave room
+      // for two workgroups on a CU: the other one's MFMAs cover a slab's first
+      // reads, so the pipeline stays within the slab.  A block is the TN MFMAs of
+      // one A fragment (row tile i) against the B fragments of a K-step; it reads
+      // the next block's A fragment and a share of the next K-step's B fragments,
+      // and a scheduling barrier closes it, so that about two blocks' fragments
+      // are live at a time.  Through the slab barriers these tiles take 3-9% more
+      // (300 products of every format pair; only FP4 x FP6 on 128x64 at long K is 2%
+      // faster so): 1829 x 1120 x 9216 on 128x128 (4,4) 69.8 us, here 65.8, (2,2) 53.9,
+      // here 47.6; 6713 x 79 x 7552 on 128x64 (4,4) 54.0, here 49.5, (2,2) 46.8, here
+      // 37.7.  256x128 gains by it as 256x256 does.
+      v8i bf[2][TN], af[2];
+      int be[TN], ae[TM];  // a lane's exponents of both K-steps (groups 2 lb and 2 lb + 1)
+      auto rd16 = [&](int off) { return (int)*reinterpret_cast<const uint16_t*>(xcur + off); };
+      auto read_b = [&](int ks, int j) {
+        bf[ks & 1][j] = op_b<FA, FB>(rd(slot_addr(CF::OFF_B, FB, b_r, j, ks)), ks);
+        if (ks == 0) be[j] = rd16(eb_lane + j * 16 * ER);
+      };
+      auto read_a = [&](int blk) {
+        const int ks = blk / TM, i = blk % TM;
+        af[blk & 1] = op_a<FA, FB>(rd(slot_addr(0, FA, a_r, i, ks)), ks);
+        if (ks == 0) ae[i] = rd16(ea_lane + i * 16 * ER);
+      };
+#pragma unroll
+      for (int j = 0; j < TN; ++j) read_b(0, j);
+      read_a(0);
+      // An FP4 slot serves both K-steps; the empty asm statements (here and
+      // between the K-steps) keep the compiler from merging their reads of it,
+      // which would hold every raw fragment for the whole slab.
+      if constexpr (FA || FB) asm volatile("" ::: "memory");
+#pragma unroll
+      for (int blk = 0; blk < 2 * TM; ++blk) {
+        const int ks = blk / TM, i = blk % TM;
+        if constexpr (FA || FB)
+          if (blk == TM) asm volatile("" ::: "memory");
+        if (blk + 1 < 2 * TM) read_a(blk + 1);
+        if (ks == 0) {
+#pragma unroll
+          for (int j = i * TN / TM; j < (i + 1) * TN / TM; ++j) read_b(1, j);
+        }
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          if (ks == 0)
+            mma<FA, FB, 0>(acc[i][j], af[blk & 1], bf[0][j], ae[i], be[j]);
+          else
+            mma<FA, FB, 1>(acc[i][j], af[blk & 1], bf[1][j], ae[i], be[j]);
+        }
+        issue_after(blk, 2 * TM);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else if constexpr (CF::G == 32) {
       // Compiler-scheduled, one K-step: per B chunk the B fragments, then each
       // A fragment against them.
       static_for<NB>([&](auto cbc) {
