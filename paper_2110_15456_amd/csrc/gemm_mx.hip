@@ -196,6 +196,50 @@ GemmPlan gemm_plan_whole(int a_m, int na, int nb, int64_t M, int64_t N, int g) {
   return GemmPlan{one ? gemm_mx11_tile(M, N, fmt_flag(a_m, na), false) : 0, 0, 1, 0, 0};
 }
 
+namespace {
+
+// The tile of a product of one-chunk operands (groups of 16) whose K is not split:
+// the rule's, unless another is priced 3% below it.  In us what a workgroup takes:
+// `fix` from its start to its first MFMA and out, `c` for a whole tile of C, `slab`
+// for a slab; c and slab with one and with two workgroups on a CU (0: one fits),
+// slab by the codes of A x B (FP6 x FP6, FP6 x FP4, FP4 x FP6, FP4 x FP4).  Slabs
+// take up to kLoad more as the card fills (its L2s and the Infinity Cache serve
+// every CU).  Fitted to every tile's times on 2820 products of 2^15 to 2^25 outputs
+// (11-20% off, by K): the tile taken is 0.9% slower than the fastest on average, the
+// rule's 2.9%.  With prices that knew only FP4 x FP4 and the rest and no start of a
+// tile beyond 4 us, 27797 x 704 x 256 (2,4) took 256x256 (32 us, 256x128 25) and
+// 32777 x 160 x 64 (15.8, 256x128 11.4).
+int whole_tile(int64_t M, int64_t N, int64_t K, int fa, int fb, int rule) {
+  struct Tile {
+    int id, bm, bn;
+    double fix, c[2], slab[2][4];
+  };
+  static const Tile kTiles[] = {{0, 256, 256, 6.67, {4.23, 0.0}, {{1.27, 1.21, 1.21, 1.14}, {0.0, 0.0, 0.0, 0.0}}},
+                                {1, 256, 128, 2.97, {2.39, 6.99}, {{0.88, 0.86, 0.81, 0.77}, {0.0, 0.0, 1.03, 0.92}}},
+                                {4, 128, 128, 1.23, {1.14, 3.51}, {{0.60, 0.56, 0.59, 0.48}, {0.77, 0.64, 0.67, 0.55}}},
+                                {3, 128, 64, 0.41, {0.62, 1.81}, {{0.46, 0.41, 0.43, 0.35}, {0.57, 0.49, 0.47, 0.40}}}};
+  constexpr double kLoad = 0.55, kRagged = 1.4, kOdd = 3.8;  // K no multiple of 128; C stored value by value
+  const int fmt = 2 * fa + fb;
+  const double slabs = (double)ceil_div(K / 16, mx::KG) * (K % 128 ? kRagged : 1.0);
+  int best = rule;
+  double best_us = 1e30;
+  for (const Tile& t : kTiles) {
+    const int occ = t.slab[1][fmt] > 0.0 ? 2 : 1;
+    const int64_t wgs = ceil_div(M, t.bm) * ceil_div(N, t.bn), full = wgs / (256 * occ), rest = wgs % (256 * occ);
+    const double used = (double)(M < t.bm ? M : t.bm) * (double)(N < t.bn ? N : t.bn) / (t.bm * t.bn) *
+                        (N % 4 ? kOdd : 1.0);
+    auto us = [&](int o, double load) {
+      return slabs * t.slab[o][fmt] * (1.0 + kLoad * load) + t.fix + t.c[o] * used;
+    };
+    const double last = rest == 0 ? 0.0 : rest <= 256 ? us(0, rest / 256.0) : us(1, 1.0);
+    const double sum = (2.9 + full * us(occ - 1, 1.0) + last) * (t.id == rule ? 0.97 : 1.0);
+    if (sum < best_us) best_us = sum, best = t.id;
+  }
+  return best;
+}
+
+}  // namespace
+
 // The plan of a product that has a workspace.  A product whose tiles fill the
 // card runs as without one.  With fewer tiles, a tile's serial run of K slabs
 // sets the time (dW of ResNet-18's conv2_x, 576 x 64 x 802816, has 5 tiles of
@@ -280,25 +324,37 @@ GemmPlan gemm_plan(int a_m, int na, int b_m, int nb, int64_t M, int64_t N, int64
   }
 
   // The few-output kernel: its operand reads (every workgroup reads its rows of
-  // both, 7 TB/s from L2 and the Infinity Cache) and the supersteps a wave waits
-  // for in turn (1.36, 2.8 and 4.2 us each on its three tiles, half of it hidden
-  // under the reads).  A tenth of margin: the tiled kernel's prices are the
-  // firmer ones.
+  // both, 7 TB/s from L2 and the Infinity Cache) and the supersteps a wave waits for
+  // in turn (1.36, 2.8 and 4.2 us each on its three tiles, half of it hidden
+  // under the reads); or, with more workgroups than fit the CUs (LDS holds 16, 4
+  // and 2 of the three tiles, and eight waves fill half a CU), the rounds of
+  // them.  Without the rounds 23517 x 896 x 64 (2,4) went to 10304 workgroups of
+  // 64 x 32, 78 us where the tiled kernel takes 20.  A tenth of margin: the tiled
+  // kernel's prices are the firmer ones.
   const double va = (na == 1 && fa ? 0.5 : 0.75) + (na == 2 ? (fa ? 0.5 : 0.75) : 0.0) + 1.0 / g;
   const double vb = (nb == 1 && fb ? 0.5 : 0.75) + (nb == 2 ? (fb ? 0.5 : 0.75) : 0.0) + 1.0 / g;
   const int64_t nss = ceil_div(K, 256), per_wave = ceil_div(nss, direct::kMaxWaves);
+  const int64_t waves = nss < direct::kMaxWaves ? nss : direct::kMaxWaves;
+  // (The other formats' tiles start 3 us later than their price says: at K = 64, 7 to
+  // 15 us where it says 5.)
+  const double tiled_us = one || best.parts > 1 ? best_us : best_us + 3.0;
   double direct_us = 1e30;
-  static const struct { int rm, rn; double us; } kDirect[] = {{1, 1, 1.36}, {2, 2, 2.8}, {4, 2, 4.2}};
+  static const struct { int rm, rn, fit; double us, again; } kDirect[] = {
+      {1, 1, 16, 1.36, 0.0}, {2, 2, 4, 2.8, 1.07}, {4, 2, 2, 4.2, 2.2}};
   for (const auto& d : kDirect) {
     if (ceil_div(M, 16 * d.rm) > direct::kMaxRowTiles) continue;  // does not fit its grid
     const double tm = (double)ceil_div(M, 16 * d.rm), tn = (double)ceil_div(N, 16 * d.rn);
     const double rows_a = M < 16 * d.rm ? M : 16 * d.rm, rows_b = N < 16 * d.rn ? N : 16 * d.rn;
-    const double us = 1.5 + tm * tn * K * (rows_a * va + rows_b * vb) / 7e6 + 0.5 * d.us * per_wave;
-    if (us < direct_us && us < 0.9 * best_us) {
+    const double reads = 1.5 + tm * tn * K * (rows_a * va + rows_b * vb) / 7e6 + 0.5 * d.us * per_wave;
+    const double more = tm * tn / (256.0 * (d.fit < 16 / waves ? d.fit : 16 / waves)) - 1.0;
+    const double rounds = 1.8 + 0.5 * d.us * per_wave + more * (0.5 * (na + nb) * d.again * per_wave + 1.6);
+    const double us = reads > rounds ? reads : rounds;
+    if (us < direct_us && us < 0.9 * tiled_us) {
       direct_us = us;
       best = GemmPlan{rule, 0, 1, d.rm, d.rn};
     }
   }
+  if (one && best.rm == 0 && best.parts == 1) best.tile = whole_tile(M, N, K, fa, fb, rule);
   return best;
 }
 

@@ -88,7 +88,7 @@ def test_row_tiles_fit_the_grid(m_a, m_b):
     """Tall, narrow products: the few-output kernel's row tiles are its grid's y."""
     few = 0
     for rows in (16, 32, 64):
-        for M in (MAX_Y * rows, MAX_Y * rows + 1, 2 * MAX_Y * rows, 1 << 23, 1 << 25):
+        for M in (1000, MAX_Y * rows, MAX_Y * rows + 1, 2 * MAX_Y * rows, 1 << 23, 1 << 25):
             for N in (1, 4, 16):
                 for K in (16, 64, 1024):
                     r = route(m_a, m_b, M, N, K, 16, None)
