@@ -468,7 +468,7 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
                                                  const uint8_t* __restrict__ b_exp, int64_t b_plane_stride, int M,
                                                  int N, int ng, float scale, float* __restrict__ C, int64_t ldc,
                                                  int tiles_m, int tiles_n, int part_slabs, int64_t part_stride,
-                                                 bool c_past, OutBFP qo) {
+                                                 OutBFP qo) {
   constexpr int TM = CF::TM, TN = CF::TN, NA = CF::NA, NB = CF::NB, FA = CF::FA, FB = CF::FB;
   // Groups of 16 with full slabs (XP): the exponents of slab pair p (slabs 2p
   // and 2p + 1: 16 contiguous bytes per row) come in one 16-byte load per row,
@@ -1408,8 +1408,8 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
     if (TN % 2 == 0 && vec && wcol + CF::WN <= N) {
       // The wave's columns all exist: pairs of 16-column tiles, lanes r and r +
       // 8 of a lane block exchanging halves, so that a store instruction writes
-      // 8 rows x 128 bytes, whole lines, which can bypass the caches (c_past; a C
-      // of hundreds of MB does not stay in them, and pushes out the operand
+      // 8 rows x 128 bytes, whole lines, which can bypass the caches (a C of
+      // hundreds of MB does not stay in them, and pushes out the operand
       // panels).  As 16 rows x 64 bytes through L2, C cost 13 us per round of
       // 256 x 256 tiles.  Measured: ffn_up (4,4) 686 -> 629 us, (6,6) 1313 ->
       // 1242; 802816 x 64 x 576 (2,2) 137 -> 92; 802816 x 576 x 64 413 -> 323;
@@ -1437,8 +1437,9 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
           }
         }
       };
-      if (c_past) store(ic<1>{});
-      else store(ic<0>{});
+      const bool lines = (ldc & 31) == 0 && (reinterpret_cast<uintptr_t>(C) & 127) == 0;
+      if (part_slabs > 0 || !lines) store(ic<0>{});
+      else store(ic<1>{});
       return;
     }
 #pragma unroll
@@ -1534,28 +1535,6 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
   }
 }
 
-// Whether C's stores bypass the caches.  Only whole lines (128 bytes) may: with
-// other rows each store writes parts of two lines, which go to memory as such
-// (2525 x 10828 x 128 (2,1) 61 us, through L2 38).  And a C with rows 16 KB apart,
-// whose lines past the caches crowd on few channels, goes through the caches
-// where it and the operands fit the Infinity Cache (256 MB; from 60 MB on: L2
-// and its write-back at the kernel's end hold a smaller one up).  Measured,
-// past the caches -> through them, one C buffer / six in turn, (4,4):
-//   8192 x 4096 x 256   46 -> 37 / 47 -> 46 us
-//   8192 x 4096 x 4096 149 -> 137 / 149 -> 145, followed by a quantize of C 176 -> 161
-//   4096 x 8192 x 1024  67 -> 55 / 67 -> 61;   (2,2) 53 -> 47 / 51 -> 51
-//   2048 x 16384 x 256  47 -> 38 / 47 -> 43
-//   2048 x 4096 x 1024 19.4 <- 20.3;  8192 x 16384 x 4096 590 <- 604
-// With rows of other lengths (22 shapes of 60 to 240 MB) past the caches is 1-6%
-// faster, with two chunk planes level (4096 x 8192 x 256 (6,6) 58 <- 60).
-template <class CF>
-inline bool c_past_caches(const float* C, int64_t ldc, int M, int N, int ng) {
-  if (ldc % 32 != 0 || reinterpret_cast<uintptr_t>(C) % 128 != 0) return false;
-  if (CF::NA != 1 || CF::NB != 1 || ldc % 4096 != 0) return true;
-  const int64_t c = 4 * (int64_t)M * ldc, ops = ((int64_t)M * (CF::FA ? 9 : 13) + (int64_t)N * (CF::FB ? 9 : 13)) * ng;
-  return c < (int64_t(60) << 20) || c + ops > (int64_t(256) << 20);
-}
-
 // part_slabs > 0: K in parts of that many slabs (an even number: the exponents
 // of slabs come in pairs), part p's sums to the M x ldc matrix at C + p M ldc.
 template <class CF, bool EXP_FULL>
@@ -1569,14 +1548,13 @@ static hipError_t launch_mx_v(const uint8_t* a_mant, const uint8_t* a_exp, int64
   const int64_t stride = (int64_t)M * ldc;
   if (!qo)
     hipLaunchKernelGGL((k_gemm_mx<CF, EXP_FULL, 0>), grid, block, 0, s, a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, M, N,
-                       ng, scale, C, ldc, tiles_m, tiles_n, part_slabs, stride,
-                       part_slabs == 0 && c_past_caches<CF>(C, ldc, M, N, ng), OutBFP{});
+                       ng, scale, C, ldc, tiles_m, tiles_n, part_slabs, stride, OutBFP{});
   else if (qo->m > 4)
     hipLaunchKernelGGL((k_gemm_mx<CF, EXP_FULL, 2>), grid, block, 0, s, a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, M, N,
-                       ng, scale, C, ldc, tiles_m, tiles_n, 0, stride, false, *qo);
+                       ng, scale, C, ldc, tiles_m, tiles_n, 0, stride, *qo);
   else
     hipLaunchKernelGGL((k_gemm_mx<CF, EXP_FULL, 1>), grid, block, 0, s, a_mant, a_exp, a_ps, b_mant, b_exp, b_ps, M, N,
-                       ng, scale, C, ldc, tiles_m, tiles_n, 0, stride, false, *qo);
+                       ng, scale, C, ldc, tiles_m, tiles_n, 0, stride, *qo);
   return hipGetLastError();
 }
 

@@ -123,28 +123,3 @@ def test_tiled_slab_counts(nslabs, g):
     for m_a, m_b in PAIRS:
         announce("tiled, %d slabs g=%d (%d,%d)" % (nslabs, g, m_a, m_b))
         check_tiled(260, 136, 128 * nslabs, g, m_a, m_b, 8000 + nslabs)
-
-
-# C's rows of whole lines (past the caches), of whole 16-byte pieces only (through
-# them) and of neither, with waves inside N and across its end.
-@pytest.mark.parametrize("N", [256, 260, 264, 270, 288, 520])
-def test_rows_of_c(N):
-    for m_a, m_b in ((4, 4), (2, 2), (2, 4), (6, 6), (6, 4), (8, 8)):
-        announce("rows of C, N=%d (%d,%d)" % (N, m_a, m_b))
-        check_tiled(300, N, 256, 16, m_a, m_b, 8100 + N)
-
-
-@pytest.mark.parametrize("m", [2, 4])
-def test_c_through_the_caches(m):
-    """60 MiB of C with rows 16 KB apart goes through the caches, half of it past
-    them: the same bits."""
-    M, N, K = 3840, 4096, 64
-    announce("C through the caches m=%d" % m)
-    gen = torch.Generator(device="cuda").manual_seed(9)
-    A, B = (fb.quantize(torch.randn((r, K), device="cuda", generator=gen), m=m) for r in (M, N))
-    C = fb.gemm(A, B, workspace=False)
-    half = fb.BFPTensor.empty(M // 2, K, 16, m, "cuda")
-    for h in (0, 1):
-        half.mant.copy_(A.mant[h * half.mant.numel():(h + 1) * half.mant.numel()])  # one plane: rows in order
-        half.exp.copy_(A.exp[h * M // 2:(h + 1) * M // 2])
-        assert torch.equal(fb.gemm(half, B, workspace=False), C[h * M // 2:(h + 1) * M // 2])
