@@ -42,6 +42,11 @@ __host__ __device__ constexpr int plane_group_bytes(int g, int m, int p) {
 constexpr int kPackedGroup = 16;
 constexpr int kPackedPlaneGroupBytes = 6;
 __host__ __device__ constexpr int64_t packed_exp_bytes(int64_t ngroups) { return 4 + 24 * ((ngroups + 63) / 64); }
+// The inverses take one quad of values per lane below this many quads, else four.
+// us at four / one (m = 8; a lane per group before: third): 2^14 values, packed 3.62
+// / 2.35 (2.67), chunk planes 3.03 / 2.28 (2.79); 2^20, 4.20 / 3.36 and 3.59 / 3.28;
+// 2^22, m = 2 chunk planes 6.45 / 6.58; 2^26 69.8 / 69.2 and 73.0 / 89.2.
+constexpr int64_t kFewQuads = int64_t(1) << 20;
 hipError_t launch_quantize_packed(const float* x, int64_t rows, int64_t len, int m, int mode, uint64_t seed,
                                   uint8_t* mant, uint8_t* exps, uint32_t* status, hipStream_t s);
 hipError_t launch_dequantize_packed(const uint8_t* mant, const uint8_t* exps, int64_t rows, int64_t len, int m,

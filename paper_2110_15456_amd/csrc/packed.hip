@@ -150,17 +150,18 @@ __global__ __launch_bounds__(256) void k_quantize_packed(const float* __restrict
 
 // y = +-q * 2^(E - 127 - (m - 1)), a lane per four consecutive values (so that
 // a wave stores 1 KB in one piece; a lane per group took 110 us on 64M values
-// at m = 4), kPdqQuads of them per lane.
-constexpr int kPdqQuads = 4;
-template <int NP>
+// at m = 4), Q of them per lane: four where the tensor fills the card, so that as
+// many loads are in flight; one on small tensors (kFewQuads, launch.h), whose time
+// is one lane's.
+template <int NP, int Q>
 __global__ __launch_bounds__(256) void k_dequantize_packed(const uint8_t* __restrict__ mant,
                                                            const uint32_t* __restrict__ expw, int64_t ngroups, int m,
                                                            float* __restrict__ y) {
-  const int64_t q0 = (int64_t)blockIdx.x * (256 * kPdqQuads) + threadIdx.x, nquads = 4 * ngroups;
+  const int64_t q0 = (int64_t)blockIdx.x * (256 * Q) + threadIdx.x, nquads = 4 * ngroups;
   const uint32_t base = packed_base(expw[0]);
-  int q[kPdqQuads][4], e[kPdqQuads];
+  int q[Q][4], e[Q];
 #pragma unroll
-  for (int i = 0; i < kPdqQuads; ++i) {
+  for (int i = 0; i < Q; ++i) {
     const int64_t at = min(q0 + 256 * i, nquads - 1), gid = at >> 2;  // (quads past the end reread the last one)
     const int k = (int)(at & 3);
     e[i] = (int)(base + packed_exponent_offset(expw, gid)) - 127 - (m - 1);
@@ -184,7 +185,7 @@ __global__ __launch_bounds__(256) void k_dequantize_packed(const uint8_t* __rest
   }
   typedef float f4 __attribute__((ext_vector_type(4)));
 #pragma unroll
-  for (int i = 0; i < kPdqQuads; ++i) {
+  for (int i = 0; i < Q; ++i) {
     const int64_t at = q0 + 256 * i;
     if (at < nquads)
       stream_store(reinterpret_cast<f4*>(y) + at, f4{ldexpf((float)q[i][0], e[i]), ldexpf((float)q[i][1], e[i]),
@@ -232,14 +233,23 @@ hipError_t launch_quantize_packed(const float* x, int64_t rows, int64_t len, int
 hipError_t launch_dequantize_packed(const uint8_t* mant, const uint8_t* exps, int64_t rows, int64_t len, int m,
                                     float* y, hipStream_t s) {
   const int64_t ngroups = rows * len / 16;
-  const dim3 grid((unsigned)((4 * ngroups + 256 * kPdqQuads - 1) / (256 * kPdqQuads)));
   const uint32_t* expw = reinterpret_cast<const uint32_t*>(exps);
+  const int64_t nquads = 4 * ngroups;
+#define FASTBFP_PDQ(NP, Q)                                                                                          \
+  hipLaunchKernelGGL((k_dequantize_packed<NP, Q>), dim3((unsigned)((nquads + 256 * Q - 1) / (256 * Q))), dim3(256), \
+                     0, s, mant, expw, ngroups, m, y)
+#define FASTBFP_PDQ_Q(NP)                     \
+  if (nquads < kFewQuads) FASTBFP_PDQ(NP, 1); \
+  else FASTBFP_PDQ(NP, 4);                    \
+  break
   switch ((m + 1) / 2) {
-    case 1: hipLaunchKernelGGL(k_dequantize_packed<1>, grid, dim3(256), 0, s, mant, expw, ngroups, m, y); break;
-    case 2: hipLaunchKernelGGL(k_dequantize_packed<2>, grid, dim3(256), 0, s, mant, expw, ngroups, m, y); break;
-    case 3: hipLaunchKernelGGL(k_dequantize_packed<3>, grid, dim3(256), 0, s, mant, expw, ngroups, m, y); break;
-    default: hipLaunchKernelGGL(k_dequantize_packed<4>, grid, dim3(256), 0, s, mant, expw, ngroups, m, y); break;
+    case 1: FASTBFP_PDQ_Q(1);
+    case 2: FASTBFP_PDQ_Q(2);
+    case 3: FASTBFP_PDQ_Q(3);
+    default: FASTBFP_PDQ_Q(4);
   }
+#undef FASTBFP_PDQ_Q
+#undef FASTBFP_PDQ
   return hipGetLastError();
 }
 

@@ -322,20 +322,20 @@ __device__ __forceinline__ void decode_quad(const uint8_t* unit, int k, int (&c)
 // instruction writes 1 KB of y in one piece: a lane per 16-value unit, which
 // stores 64 bytes in four pieces 64 bytes apart from its neighbours', took 95
 // us on 64M values of m = 4, g = 16 (3.4 TB/s) and 157 at g = 64; now 59 and 58
-// (5.5 TB/s).  kDeqQuads quads per lane keep that many loads in
-// flight.  P0 / P1: the plane formats (launch.h); with two planes q = c0 * 2^s
+// (5.5 TB/s).  Q quads per lane: four where the tensor fills the card, so that
+// as many loads are in flight; one on small tensors (kFewQuads), whose time is one
+// lane's.  P0 / P1: the plane formats (launch.h); with two planes q = c0 * 2^s
 // + c1, s = 2 when plane 1 is a Lo2 plane and 4 otherwise (both chunks carry
 // the sign).  gsh: log2 of the quads in a group.
-constexpr int kDeqQuads = 4;
-template <int NCH, int P0, int P1>
+template <int NCH, int P0, int P1, int Q>
 __global__ __launch_bounds__(256) void k_dequantize(const uint8_t* __restrict__ mant, const uint8_t* __restrict__ exps,
                                                     int64_t nquads, int gsh, int m, float* __restrict__ y) {
   constexpr int B0 = P0 != kPlaneFP6 ? 8 : 12, B1 = P1 != kPlaneFP6 ? 8 : 12;  // bytes per unit
-  const int64_t q0 = (int64_t)blockIdx.x * (256 * kDeqQuads) + threadIdx.x;
+  const int64_t q0 = (int64_t)blockIdx.x * (256 * Q) + threadIdx.x;
   const uint8_t* mant1 = mant + nquads / 4 * B0;
-  int c[kDeqQuads][4], e[kDeqQuads];
+  int c[Q][4], e[Q];
 #pragma unroll
-  for (int i = 0; i < kDeqQuads; ++i) {
+  for (int i = 0; i < Q; ++i) {
     const int64_t q = min(q0 + 256 * i, nquads - 1);  // (quads past the end reread the last one)
     const int k = (int)(q & 3);
     decode_quad<P0>(mant + (q >> 2) * B0, k, c[i]);
@@ -349,7 +349,7 @@ __global__ __launch_bounds__(256) void k_dequantize(const uint8_t* __restrict__ 
   }
   typedef float f4 __attribute__((ext_vector_type(4)));
 #pragma unroll
-  for (int i = 0; i < kDeqQuads; ++i) {
+  for (int i = 0; i < Q; ++i) {
     const int64_t q = q0 + 256 * i;
     if (q < nquads)
       stream_store(reinterpret_cast<f4*>(y) + q, f4{ldexpf((float)c[i][0], e[i]), ldexpf((float)c[i][1], e[i]),
@@ -696,8 +696,12 @@ hipError_t launch_weight_update(const float* w, const float* dw, float alpha, fl
 template <int NCH, int P0, int P1 = kPlaneFP6>
 static hipError_t launch_deq_t(const uint8_t* mant, const uint8_t* exps, int64_t nquads, int gsh, int m, float* y,
                                hipStream_t s) {
-  const unsigned blocks = (unsigned)((nquads + 256 * kDeqQuads - 1) / (256 * kDeqQuads));
-  hipLaunchKernelGGL((k_dequantize<NCH, P0, P1>), dim3(blocks), dim3(256), 0, s, mant, exps, nquads, gsh, m, y);
+  if (nquads < kFewQuads)
+    hipLaunchKernelGGL((k_dequantize<NCH, P0, P1, 1>), dim3((unsigned)((nquads + 255) / 256)), dim3(256), 0, s, mant,
+                       exps, nquads, gsh, m, y);
+  else
+    hipLaunchKernelGGL((k_dequantize<NCH, P0, P1, 4>), dim3((unsigned)((nquads + 1023) / 1024)), dim3(256), 0, s, mant,
+                       exps, nquads, gsh, m, y);
   return hipGetLastError();
 }
 

@@ -98,6 +98,19 @@ def test_row_tiles_fit_the_grid(m_a, m_b):
     assert few > 0
 
 
+# Many outputs, short K: rounds upon rounds of the few-output kernel's workgroups.
+@pytest.mark.parametrize("m_a,m_b,M,N,K", [(2, 4, 23517, 896, 64), (2, 4, 2366, 13536, 64), (2, 4, 50589, 320, 64),
+                                           (4, 2, 64994, 384, 16), (4, 8, 62361, 512, 64), (8, 8, 22816, 1360, 64)])
+def test_many_outputs_stay_on_the_tiled_kernel(m_a, m_b, M, N, K):
+    assert route(m_a, m_b, M, N, K, 16, None)[0] >= 0
+
+
+# Mixed codes with a short K: not on the largest tile.
+@pytest.mark.parametrize("M,N,K", [(27797, 704, 256), (6855, 2368, 192), (57242, 384, 192), (3004, 6944, 384)])
+def test_mixed_codes_on_a_smaller_tile(M, N, K):
+    assert route(2, 4, M, N, K, 16, None)[0] in (1, 3, 4)
+
+
 def test_route_arguments():
     lib = _lib.load()
     out = [ctypes.byref(ctypes.c_int(0)) for _ in range(4)]

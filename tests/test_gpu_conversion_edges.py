@@ -1,5 +1,5 @@
 """Block edges of the column quantizer (8 unit rows x 64 columns per block) and
-of the dequantizer (1024 quads per block), bit-exact against the oracle."""
+of the dequantizer (256 or 1024 quads per block), bit-exact against the oracle."""
 from __future__ import annotations
 
 import numpy as np
@@ -29,7 +29,7 @@ def test_column_blocks(g, units):
 
 @pytest.mark.parametrize("g", [4, 16, 64])
 def test_dequantize_blocks(g):
-    """64 and 65 units of 64 values: one block's quads, and one unit more."""
+    """64 and 65 units of 64 values: whole blocks' quads, and one unit more."""
     for rows in (1, 64, 65, 129):
         for m in (2, 4, 6, 8):
             announce("dequantize blocks g=%d rows=%d m=%d" % (g, rows, m))
@@ -38,6 +38,20 @@ def test_dequantize_blocks(g):
             q, E, _ = oracle.quantize(x, g=g, m=m, threads=THREADS)
             out = torch.full((rows, 64), float("nan"), device="cuda")
             assert np.array_equal(fb.dequantize(t, out=out).cpu().numpy(), oracle.dequantize(q, E, g, m))
+
+
+def test_dequantize_many():
+    """2^20 quads and a few more: four per lane, the last block not whole."""
+    rows = 65537
+    x = synth.draw("grads", (rows, 64), 950)
+    xt = torch.from_numpy(x).cuda()
+    for m in (2, 4, 6, 8):
+        announce("dequantize %d x 64 m=%d" % (rows, m))
+        t = fb.quantize(xt, g=16, m=m)
+        q, E, _ = oracle.quantize(x, g=16, m=m, threads=THREADS)
+        assert np.array_equal(fb.dequantize(t).cpu().numpy(), oracle.dequantize(q, E, 16, m))
+        p = fb.quantize_packed(xt, m=m)
+        assert torch.equal(fb.dequantize_packed(p), fb.dequantize(fb.repack(p)))
 
 
 @pytest.mark.parametrize("m", range(1, 9))

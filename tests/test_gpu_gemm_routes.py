@@ -123,3 +123,12 @@ def test_tiled_slab_counts(nslabs, g):
     for m_a, m_b in PAIRS:
         announce("tiled, %d slabs g=%d (%d,%d)" % (nslabs, g, m_a, m_b))
         check_tiled(260, 136, 128 * nslabs, g, m_a, m_b, 8000 + nslabs)
+
+
+# C's rows of whole lines (past the caches), of whole 16-byte pieces only (through
+# them) and of neither, with waves inside N and across its end.
+@pytest.mark.parametrize("N", [256, 260, 264, 270, 288, 520])
+def test_rows_of_c(N):
+    for m_a, m_b in ((4, 4), (2, 2), (2, 4), (6, 6), (6, 4), (8, 8)):
+        announce("rows of C, N=%d (%d,%d)" % (N, m_a, m_b))
+        check_tiled(300, N, 256, 16, m_a, m_b, 8100 + N)
