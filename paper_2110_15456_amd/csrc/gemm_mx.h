@@ -480,6 +480,8 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
   constexpr bool X3 = NA == 2 && NB == 2 && CF::G == 16 && !FA && !FB;
   // an operand split at 2 bits fills whole MFMA blocks (groups of 16)
   constexpr bool COMB = CF::G == 16 && ((NA == 2 && FA) || (NB == 2 && FB));
+  // ... against one plane of FP6 codes: the pipeline within the slab
+  constexpr bool COMBL = COMB && ((NA == 1 && !FA) || (NB == 1 && !FB));
   // explicit pipeline of the two-chunk loop (one operand split at 4 bits)
   constexpr bool PIPE2 = (NA == 2 || NB == 2) && CF::G == 16 && !X3 && !COMB;
   constexpr int NTHR = CF::NT;
@@ -877,7 +879,7 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
         mma_drain(acc);
       }
     }
-  } else if constexpr (COMB) {
+  } else if constexpr (COMB && !COMBL) {
     // An operand split at 2 bits (q = 4 (q >> 2) + (q & 3)) fills a whole
     // 32-value MFMA block with one group of 16: the codes of +-(q >> 2)/2 (its
     // FP6 plane) in half 0 and those of +-(q & 3)/8 (its Lo2 plane, unpacked) in
@@ -897,8 +899,8 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
     // half, D's second copy) is built a block ahead, in the shadow of this
     // block's MFMAs, in the tuples that the LDS reads fill.  Against reading each
     // slab's first fragments after its barrier and building D's copies between the
-    // K-steps, 8192 x 16384 x 4096: (6,6) 1330 -> 1240 us, (6,4) 1230 -> 1123, (6,2)
-    // 917 -> 857, (6,8) 2262 -> 1909; 2048^3 (6,6) 42 -> 39.5.
+    // K-steps, 8192 x 16384 x 4096: (6,6) 1330 -> 1240 us, (6,8) 2262 -> 1909; 2048^3
+    // (6,6) 42 -> 39.5.  (Against one plane of FP6 codes it is slower: below.)
     constexpr bool CA = NA == 2 && FA;
     constexpr int TC = CA ? TM : TN, TD = CA ? TN : TM, ND = CA ? NB : NA;
     constexpr int C0 = CA ? mx::a_plane<CF>(0) : mx::b_plane<CF>(0);  // FP6 plane of q >> 2
@@ -997,7 +999,10 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
     };
-    constexpr int NPART = NLOAD < FASTBFP_MX_SPREAD ? NLOAD : FASTBFP_MX_SPREAD;
+    // (Against one plane of FP4 codes six parts, over 13 products of (6,2) and (2,6)
+    // 1.3% faster than eight: 12688 x 2080 x 2816 (2,6) 153 -> 148 us.)
+    constexpr int SPREAD = ND == 1 && FASTBFP_MX_SPREAD > 6 ? 6 : FASTBFP_MX_SPREAD;
+    constexpr int NPART = NLOAD < SPREAD ? NLOAD : SPREAD;
     constexpr int EARLY = L < NPART ? L : NPART;
     // One load part per block from block 0 on needs NPART - EARLY blocks; with
     // few blocks two go together.
@@ -1257,6 +1262,67 @@ __global__ __launch_bounds__(CF::NT, CF::WAVES) void k_gemm_mx(const uint8_t* __
         issue_after(blk, 2 * TM);
         __builtin_amdgcn_sched_barrier(0);
       }
+    } else if constexpr (COMBL) {
+      // An operand split at 2 bits (C: whole blocks, as above) against one plane of
+      // FP6 codes (D, repeated): a block is one C fragment of a K-step against every
+      // D fragment.  It reads the next block's C slots, and K-step 0's blocks a share
+      // of K-step 1's D slots; D's copies are made at the start of each K-step.  With
+      // one MFMA per fragment pair a slab is too short for the loads that the pipeline
+      // through the slab barriers leaves to its first blocks: 8192 x 4096 x 4096 (6,4)
+      // 284 us, here 265; (4,6) 291, here 274; 2285 x 2648 x 5632 (6,4) 94, here 86.
+      constexpr bool CA = NA == 2;
+      constexpr int TC = CA ? TM : TN, TD = CA ? TN : TM;
+      constexpr int C0 = CA ? mx::a_plane<CF>(0) : mx::b_plane<CF>(0);  // FP6 plane of q >> 2
+      constexpr int C1 = CA ? mx::a_plane<CF>(1) : mx::b_plane<CF>(1);  // Lo2 plane of q & 3
+      constexpr int D0 = CA ? mx::b_plane<CF>(0) : mx::a_plane<CF>(0);
+      const int c_r = CA ? a_r : b_r, d_r = CA ? b_r : a_r;
+      const int c_e = CA ? ea_lane : eb_lane, d_e = CA ? eb_lane : ea_lane;
+      u32x4 dr[2][TD], ch[2], cl[TC];  // D's slots by K-step, C's FP6 slots by block, its Lo2 slots (both K-steps)
+      v8i dd[TD];                      // D's operands of the current K-step
+      int ce[TC], de[TD];              // both K-steps' exponents; the combined block weighs 2, half of it on each side
+      auto rd16 = [&](int off) { return (int)*reinterpret_cast<const uint16_t*>(xcur + off); };
+      auto read_d = [&](int ks, int t) {
+        dr[ks][t] = rd(slot_addr(D0, 0, d_r, t, ks));
+        if (ks == 0) de[t] = rd16(d_e + t * 16 * ER) + 0x0101;
+      };
+      auto read_c = [&](int blk) {
+        const int ks = blk / TC, c = blk % TC;
+        ch[blk & 1] = rd(slot_addr(C0, 0, c_r, c, ks));
+        if (ks == 0) {
+          cl[c] = rd(slot_addr(C1, 1, c_r, c, 0));
+          ce[c] = rd16(c_e + c * 16 * ER);
+        }
+      };
+#pragma unroll
+      for (int t = 0; t < TD; ++t) read_d(0, t);
+      read_c(0);
+      static_for<2 * TC>([&](auto bc) {
+        constexpr int blk = decltype(bc)::value, ks = blk / TC, c = blk % TC;
+        if constexpr (c == 0) {
+#pragma unroll
+          for (int t = 0; t < TD; ++t) {
+            const u32x4& x = dr[ks][t];
+            dd[t] = v8i{(int)x[0], (int)x[1], (int)x[2], (int)x[0], (int)x[1], (int)x[2], 0, 0};
+          }
+        }
+        if constexpr (blk + 1 < 2 * TC) read_c(blk + 1);
+        if constexpr (ks == 0) {
+#pragma unroll
+          for (int t = c * TD / TC; t < (c + 1) * TD / TC; ++t) read_d(1, t);
+        }
+        uint32_t t0, t1, t2;
+        lo2_unpack(cl[c][2 * ks], cl[c][2 * ks + 1], t0, t1, t2);
+        const u32x4& h = ch[blk & 1];
+        const v8i cv = v8i{(int)h[0], (int)h[1], (int)h[2], (int)t0, (int)t1, (int)t2, 0, 0};
+        const int e_c = ce[c] + 0x0101;  // (the bytes stay below 256 for exponents up to 250)
+#pragma unroll
+        for (int t = 0; t < TD; ++t) {
+          if constexpr (CA) mma<0, 0, ks>(acc[c][t], cv, dd[t], e_c, de[t]);
+          else mma<0, 0, ks>(acc[t][c], dd[t], cv, de[t], e_c);
+        }
+        issue_after(blk, 2 * TC);
+        __builtin_amdgcn_sched_barrier(0);
+      });
     } else if constexpr (CF::G == 32) {
       // Compiler-scheduled, one K-step: per B chunk the B fragments, then each
       // A fragment against them.
