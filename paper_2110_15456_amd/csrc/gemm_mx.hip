@@ -249,14 +249,14 @@ int whole_tile(int64_t M, int64_t N, int64_t K, int fa, int fb, int rule) {
 // of every tile x parts and of the few-output kernel's tiles over weight
 // gradients, few-token and small products on MI355X.  What the plan takes, and
 // its time against bfp_gemm's (graph replays of ten calls):
-//   576 x 64 x 802816 (2,2)     4204 -> 89  (128x64 in 102 parts)
-//   2304 x 256 x 50176 (4,4)     285 -> 54  (256x128 in 14 parts)
-//   1024 x 4096 x 16384 (4,4)    136 -> 88  (256x256 in 4 parts)
+//   576 x 64 x 802816 (2,2)     3949 -> 83  (128x64 in 102 parts)
+//   2304 x 256 x 50176 (4,4)     264 -> 56  (256x128 in 14 parts)
+//   1024 x 4096 x 16384 (4,4)    127 -> 87  (256x256 in 4 parts)
 //   1024 x 1024 x 8192 (6,6)     134 -> 39  (256x128 in 8 parts)
-//   16 x 16384 x 4096 (4,4)       25 -> 17  (few-output, 32 x 32)
-//   1 x 4096 x 4096 (4,4)         17 -> 5.1 (few-output, 16 x 16)
-//   256 x 256 x 256 (4,4)        5.2 -> 3.0 (few-output, 16 x 16)
-//   2048 x 1024 x 4096 (4,4)      25 -> 24  (whole, 128x64; any split 30 or more)
+//   16 x 16384 x 4096 (4,4)       24 -> 18  (few-output, 32 x 32)
+//   1 x 4096 x 4096 (4,4)         18 -> 5.4 (few-output, 16 x 16)
+//   256 x 256 x 256 (4,4)        5.2 -> 3.2 (few-output, 16 x 16)
+//   2048 x 1024 x 4096 (4,4)      25 -> 25  (whole, 128x64; any split 30 or more)
 GemmPlan gemm_plan(int a_m, int na, int b_m, int nb, int64_t M, int64_t N, int64_t K, int g) {
   const int fa = fmt_flag(a_m, na), fb = fmt_flag(b_m, nb);
   const bool one = na == 1 && nb == 1 && g == 16;
