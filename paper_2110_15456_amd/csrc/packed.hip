@@ -26,8 +26,12 @@ __global__ void k_packed_header_clear(uint32_t* hdr) { *hdr = 0u; }
 // (four independent loads per thread and round).  Two blocks a CU: with 2048
 // blocks (64 KB each) the conversion of 8192 x 4096 at m = 4 took 74 us, with
 // 1024 62, 512 57, 256 66 (and 62, 58, 60 with 1024-thread blocks at 512, 256,
-// 128); on 2048^2 25 us with 1024 blocks, 16 with 512 or 256.
-constexpr int kExpMaxBlocks = 512;
+// 128); on 2048^2 25 us with 1024 blocks, 16 with 512 or 256.  At least two rounds
+// a block: below 1024 rounds the time goes with the number of blocks, each with an
+// access to the one word.  The conversion of 1536 x 1024 took 12.8 us with single
+// rounds, 10.1 with two, 10.8 with four; of 2048 x 1024 14.6, 10.9 and 11.8; of
+// 512 x 1024 9.1, 8.8, 9.1.
+constexpr int kExpMaxBlocks = 512, kExpMaxRounds = 2;
 __global__ __launch_bounds__(256) void k_exponent_max(const u32x4* __restrict__ x, int64_t n4, int64_t rounds,
                                                       uint32_t* hdr) {
   uint32_t e = 0;
@@ -220,7 +224,8 @@ hipError_t launch_quantize_packed(const float* x, int64_t rows, int64_t len, int
   // E_max of the tensor first (the base every group's exponent is stored above)
   hipLaunchKernelGGL(k_packed_header_clear, dim3(1), dim3(1), 0, s, expw);
   const int64_t n4 = n / 4;
-  const int64_t all = (n4 + 1023) / 1024, rounds = (all + kExpMaxBlocks - 1) / kExpMaxBlocks;
+  const int64_t all = (n4 + 1023) / 1024, even = (all + kExpMaxBlocks - 1) / kExpMaxBlocks;
+  const int64_t rounds = even < kExpMaxRounds ? kExpMaxRounds : even;
   hipLaunchKernelGGL(k_exponent_max, dim3((unsigned)((all + rounds - 1) / rounds)), dim3(256), 0, s,
                      reinterpret_cast<const u32x4*>(x), n4, rounds, expw);
   hipError_t e = hipGetLastError();

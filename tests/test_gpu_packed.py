@@ -105,6 +105,26 @@ def test_packed_edge_cases():
     assert int(st.item()) & 1
 
 
+@pytest.mark.parametrize("rounds", [1, 2, 3, 1023, 1024, 1025, 1537])
+def test_packed_largest_exponent(rounds):
+    """The largest exponent is found at the first and last value of the tensor
+    and on either side of the edges of the maximum's rounds of 4096 values and
+    of its blocks' (two rounds, then three above 1024 rounds)."""
+    for n in (4096 * rounds - 16, 4096 * rounds, 4096 * rounds + 16):
+        announce("quantize_packed E_max of %d values" % n)
+        x = torch.ones((n // 16, 16), device="cuda")
+        flat = x.view(-1)
+        edges = [0, 4096, 8192, 12288, 4096 * (rounds - 1), n - 16, n]
+        for at in sorted({e + d for e in edges for d in (-1, 0) if 0 <= e + d < n}):
+            flat[at] = 2.0 ** 9
+            t = fb.quantize_packed(x, m=2)
+            flat[at] = 1.0
+            emax = int(t.exp[:4].cpu().numpy().view(np.uint32)[0])
+            assert emax == 127 + 9, at
+        t = fb.quantize_packed(x, m=2)
+        assert int(t.exp[:4].cpu().numpy().view(np.uint32)[0]) == 127
+
+
 @pytest.mark.parametrize("m", [1, 2, 4, 5, 6, 8])
 def test_dequantize_packed(m):
     x = wide_range((33, 512), 30 + m)
